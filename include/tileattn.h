@@ -319,6 +319,38 @@ ta_status ssd_chunk_scan(const void *x, const void *Cm, const float *cb, const f
                          int dstate, int chunk_size, void *stream);
 
 /*
+ * ssd_forward — the whole chunked forward in one call: y and the final states
+ * of the recurrence above, without the intermediate states, cb or entering
+ * states of the four functions in memory (each workgroup walks a head's
+ * sequence with the state in registers).  Same inputs, outputs and precision
+ * as the four chained: bf16 operands of the contractions, fp32 sums and state.
+ *
+ *   out          device, fp32 [batch, L, nheads, headdim]        written
+ *   final_states device, fp32 [batch, nheads, headdim, dstate], or NULL
+ *   num_segments 1..64: the sequence is cut into this many segments (whole
+ *                steps of 64 positions; trailing empty ones are dropped) that
+ *                run in parallel, for calls with too few heads to fill the
+ *                GPU; for more than one, a first kernel writes the state each
+ *                segment adds to `workspace` (device, 16-byte aligned, at
+ *                least ssd_forward_workspace_bytes(...) bytes, owned by the
+ *                caller, no overlap with any other argument;
+ *                TA_ERR_WORKSPACE if NULL or smaller); 1 ignores it
+ *   nheads <= 131072 and L <= 2^30 (else TA_ERR_INVALID_SHAPE); other
+ *   arguments and status codes as the chunk functions
+ */
+ta_status ssd_forward(const void *x, const void *Bm, const void *Cm, const float *dt, const float *A,
+                      const float *D, float *out, float *final_states, int batch, int seqlen,
+                      int nheads, int ngroups, int headdim, int dstate, int num_segments,
+                      void *workspace, size_t workspace_bytes, void *stream);
+
+/* Workspace bytes ssd_forward needs for num_segments (0 for one).  No HIP call. */
+ta_status ssd_forward_workspace_bytes(int batch, int seqlen, int nheads, int num_segments,
+                                      size_t *bytes);
+
+/* A segment count for ssd_forward.  No HIP call. */
+ta_status ssd_segment_heuristic(int batch, int seqlen, int nheads, int *num_segments);
+
+/*
  * ta_schedule — host-side tile schedule of attn_fwd, for tests and tools.
  * For the query tile `q_tile` (rows q_tile*BM .. q_tile*BM+BM-1, BM from
  * ta_tile_shape) it reports how many key tiles of BN keys the kernel visits

@@ -659,6 +659,480 @@ __global__ __launch_bounds__(NT, 4) void state_passing_kernel(PassArgs args)
     }
 }
 
+// ---------------------------------------------------------------------------
+// The whole forward in one pass: y and the final states of the recurrence
+//   h_t = exp(dt_t A) h_{t-1} + dt_t x_t Bm_t^T,  y_t = h_t Cm_t + D x_t.
+//
+// The chained functions above move every chunk state through memory four
+// times and x twice, 9.7 GB at B=64 L=2048 H=64 where x, Bm, Cm, dt and y are
+// 3.5.  Here a workgroup of four waves walks the sequence of one or two heads
+// (NH) of a group in steps of FQ = 64 positions with the state in registers
+// (fp32), so x is read and y written once and nothing else moves: 2.06 ms ->
+// 0.96 ms there.  The same traffic without the arithmetic takes 0.58 ms, the
+// arithmetic without the stores 0.75: what bounds it is the instructions of
+// the two waves that share a SIMD (VALU issue 48 %, matrix cores 25 % of the
+// time) and their waits on each other.
+//  * A head's state S^T[n][p] and y^T[p][l] are split over 4 / NH waves, 16 NH
+//    head dims each (16 x 16 accumulator blocks, lane = dim p of the state,
+//    position l of y).  The state is the A operand of the entering-state term
+//    straight from the accumulators: k-slot t of lane group g of two adjacent
+//    blocks stands for n = 32 kk + 4 g + t (t < 4) or 32 kk + 16 + 4 g + t - 4,
+//    and the C tile is stored in that order.
+//  * The state enters as two bf16 numbers, S rounded and the rest rounded (two
+//    MFMAs), so that shortening the chunk from 256 to 64 positions, which
+//    sends more of y through the state, costs no precision: every term of y
+//    is rounded once (the weighted x, or the within-step weight).  Error
+//    against 64 bits at B=2 L=1000 H=512: 1.20e-3 for y and 1.66e-3 for the
+//    states, as the chained functions.
+//  * A step reads the C tile once for both that term and the blocks of
+//    C B^T, whose weighted form (bf16, in LDS) the waves exchange; every tile
+//    is dead at the barrier behind it, so that a step has two barriers.
+//  * The next step's tiles are loaded into registers during the current one,
+//    and y leaves by range-checked buffer stores: a branch around them would
+//    make the wait for the tiles one for the stores as well.
+// STATE_ONLY: the same walk without C and y, for the state of a segment
+// started from zero (see ssd_forward).
+
+constexpr int FQ = 64;                    // positions per step
+constexpr int FX_BYTES = FQ * SP * 2;     // one head's x tile
+constexpr int FB_BYTES = FQ * SN * 2;     // B or C tile
+constexpr int FM_BYTES = FQ * FQ * 2;     // one head's weight tile
+
+struct FwdArgs {
+    SsdShape s;
+    const uint16_t *x, *Bm, *Cm;
+    const float *dt, *A, *D;
+    float *out, *final_states;
+    float *seg_states;   // [B][nseg - 1][H] tiles of SP * SN floats, in accumulator order
+    float *seg_decay;    // [B][nseg - 1][H] log2 of the segment's decay
+    int nseg, seg_steps; // segments of the sequence, steps per segment
+    int n_wg;
+};
+
+// 16-byte chunk swizzles of the three row-major tiles, chosen so that the
+// transpose reads (eight rows of 32 bytes per half wave) and the row reads
+// (16 rows) of each are free of bank conflicts
+__device__ __forceinline__ int swz_fx(int r) { return 2 * ((r >> 1) & 1) + 4 * ((r >> 3) & 1); }
+__device__ __forceinline__ int swz_fb(int r)
+{
+    return 2 * (r & 3) + 8 * ((r >> 3) & 1) + ((r >> 2) & 1);
+}
+__device__ __forceinline__ int swz_fc(int r) { return r & 15; }
+__device__ __forceinline__ int swz_fm(int r) { return (r >> 1) & 7; }
+
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// Transpose read for 16 x 16 x 32 MFMAs: lane l gets eight k-slots of its
+// column, four rows read at p0 and the next four at p1.
+__device__ __forceinline__ bf16x8 tr_operand16(const unsigned char *p0, const unsigned char *p1)
+{
+    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4 *)p0);
+    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4 *)p1);
+    const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
+    return __builtin_bit_cast(bf16x8, u32x4{l2[0], l2[1], h2[0], h2[1]});
+}
+
+__device__ __forceinline__ float lane_value(float v, int lane)
+{
+    return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), lane));
+}
+
+// inclusive prefix sum over a wave's 64 lanes, in registers (DPP row shifts
+// within each row of 16, then the rows' last lanes broadcast onward)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_add(float v)
+{
+    return v + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, ROWS, 0xF, true));
+}
+__device__ __forceinline__ float wave_scan(float v)
+{
+    v = dpp_add<0x111, 0xF>(v);   // row_shr 1, 2, 4, 8
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);   // row_bcast 15 to rows 1 and 3
+    v = dpp_add<0x143, 0xC>(v);   // row_bcast 31 to rows 2 and 3
+    return v;
+}
+
+// Buffer access to rows t0, t0 + 1, .. of a [L][row_bytes] slice seen from
+// column byte `col` on (base: row 0, that column): everything from row L on
+// is out of range, loads there return zero and stores are dropped.  No
+// branch surrounds these accesses, so a step's wait for its tiles does not
+// also wait for the previous step's stores.
+typedef __amdgpu_buffer_rsrc_t brsrc_t;
+template <typename T>
+__device__ __forceinline__ brsrc_t range_rsrc(T *base, int t0, int L, size_t row_bytes, size_t col)
+{
+    const size_t left = t0 < L ? (size_t)(L - t0) * row_bytes - col : 0;
+    return __builtin_amdgcn_make_buffer_rsrc((void *)((uintptr_t)base + (size_t)t0 * row_bytes), 0,
+                                             (int)(uint32_t)min(left, (size_t)0xFFFFFFFFu), 0x00020000);
+}
+constexpr int AUX_NT = 2;   // the non-temporal cache policy
+template <bool NT>
+__device__ __forceinline__ u32x4 buf_load(brsrc_t r, uint32_t off)
+{
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, NT ? AUX_NT : 0));
+}
+template <bool NT>
+__device__ __forceinline__ void buf_store(brsrc_t r, uint32_t off, f32x4 v)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, off, 0, NT ? AUX_NT : 0);
+}
+
+template <int NH, bool STATE_ONLY, bool STREAM>
+__global__ __launch_bounds__(NT, NH == 1 ? 3 : 2) void ssd_forward_kernel(FwdArgs args)
+{
+    const FwdArgs &a = args;
+    constexpr int PB = NH, WPH = 4 / NH;     // waves per head, 16 PB head dims each
+    constexpr int XPT = FQ * 8 * NH / NT;    // 16-byte chunks of x per thread and step
+    constexpr int BPT = FQ * 16 / NT;        // ... of B, and of C
+    __shared__ __attribute__((aligned(16))) unsigned char xt[NH * FX_BYTES], bt[FB_BYTES];
+    __shared__ __attribute__((aligned(16))) unsigned char ct[STATE_ONLY ? 16 : FB_BYTES];
+    __shared__ __attribute__((aligned(16))) unsigned char mt[STATE_ONLY ? 16 : NH * FM_BYTES];
+    // per step parity and head: log2 of the decay up to each position, dt,
+    // and the weight exp(a_last - a_l) dt_l of a position in the new state
+    __shared__ __attribute__((aligned(16))) float a2s[2][NH][FQ], dts[2][NH][FQ], wst[2][NH][FQ];
+    __shared__ __attribute__((aligned(16))) float fss[2][NH][FQ];   // see the blocks under the diagonal
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int w4 = wave, hi = wave / WPH, w = wave % WPH;   // the wave's head and dims 16 PB w ..
+    const int g = lane >> 4, c16 = lane & 15;
+
+    const int hgs = a.s.H / NH;
+    const int nseg = STATE_ONLY ? a.nseg - 1 : a.nseg;
+    const int logical = xcd_logical(blockIdx.x, a.n_wg);
+    const int h0 = (logical % hgs) * NH;
+    const int seg = (logical / hgs) % nseg;
+    const int b = logical / (hgs * nseg);
+    const int grp = h0 / a.s.hpg;
+    const int h = h0 + hi;
+    const int L = a.s.L;
+    const int t_lo = seg * a.seg_steps * FQ;                       // first position
+    const int t_hi = min(L, t_lo + a.seg_steps * FQ);              // past its last one
+
+    const size_t xrow = (size_t)a.s.H * SP, brow = (size_t)a.s.G * SN;
+    const float *dtp = a.dt + (size_t)b * L * a.s.H + h;
+    const uint16_t *xb = a.x + (size_t)b * L * xrow + (size_t)h0 * SP;
+    const uint16_t *bb = a.Bm + (size_t)b * L * brow + (size_t)grp * SN;
+    const uint16_t *cb = STATE_ONLY ? nullptr : a.Cm + (size_t)b * L * brow + (size_t)grp * SN;
+
+    // A step's tiles by buffer loads whose range ends with the segment:
+    // positions past it read as zero.  This thread's chunk i: row r + i RX of
+    // the NH heads' 8 NH x chunks, row r + 16 i of B's and C's 16.  The
+    // decays' dt comes first: it is waited for before the tiles.
+    constexpr int RX = NT / (8 * NH);
+    const int rxt = tid / (8 * NH), cxt = tid % (8 * NH), rbt = tid >> 4, cbt = tid & 15;
+    const uint32_t xpitch = (uint32_t)(xrow * 2), bpitch = (uint32_t)(brow * 2), ypitch = (uint32_t)(xrow * 4);
+    const uint32_t xgo = rxt * xpitch + cxt * 16, bgo = rbt * bpitch + cbt * 16;
+    const uint32_t dgo = lane * (uint32_t)(a.s.H * 4);
+    const uint32_t ygo = c16 * ypitch + (16 * PB * w + 4 * g) * 4;
+    u32x4 nx[XPT], nb[BPT], nc[STATE_ONLY ? 1 : BPT];
+    float ndt;
+    auto load_tiles = [&](int t0) {
+        const brsrc_t rd = range_rsrc(dtp, t0, t_hi, a.s.H * (size_t)4, h * 4);
+        const brsrc_t rx = range_rsrc(xb, t0, t_hi, xrow * 2, h0 * (SP * 2));
+        const brsrc_t rb = range_rsrc(bb, t0, t_hi, brow * 2, grp * (SN * 2));
+        ndt = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rd, dgo, 0, 0));
+#pragma unroll
+        for (int i = 0; i < XPT; ++i)
+            nx[i] = buf_load<STREAM>(rx, xgo + i * RX * xpitch);
+#pragma unroll
+        for (int i = 0; i < BPT; ++i)
+            nb[i] = buf_load<false>(rb, bgo + i * 16 * bpitch);
+        if (!STATE_ONLY) {
+            const brsrc_t rc = range_rsrc(cb, t0, t_hi, brow * 2, grp * (SN * 2));
+#pragma unroll
+            for (int i = 0; i < BPT; ++i)
+                nc[i] = buf_load<false>(rc, bgo + i * 16 * bpitch);
+        }
+    };
+    // Their places in the tiles (the swizzles repeat every 16 rows).  C's
+    // columns n = 8 cbt .. +7 go as two runs of four, each 32-column block
+    // ordered [g][half]: run q of the block (q = n / 4 % 8) is half q / 4 of
+    // chunk g = q % 4.
+    static_assert(RX % 16 == 0, "the swizzles repeat every 16 rows");
+    const uint32_t xst = (cxt / 8) * FX_BYTES + rxt * (SP * 2) + ((cxt % 8) ^ swz_fx(rxt)) * 16;
+    const uint32_t bst = rbt * (SN * 2) + (cbt ^ swz_fb(rbt)) * 16;
+    const int cq = 4 * (cbt >> 2) + ((2 * cbt) & 3);
+    const uint32_t cst = rbt * (SN * 2) + (cq ^ swz_fc(rbt)) * 16 + 8 * ((cbt >> 1) & 1);
+    auto store_tiles = [&]() {
+#pragma unroll
+        for (int i = 0; i < XPT; ++i)
+            *(u32x4 *)(xt + xst + i * (RX * SP * 2)) = nx[i];
+#pragma unroll
+        for (int i = 0; i < BPT; ++i) {
+            *(u32x4 *)(bt + bst + i * (16 * SN * 2)) = nb[i];
+            if (!STATE_ONLY) {
+                *(u32x2 *)(ct + cst + i * (16 * SN * 2)) = u32x2{nc[i][0], nc[i][1]};
+                *(u32x2 *)(ct + (cst ^ 16) + i * (16 * SN * 2)) = u32x2{nc[i][2], nc[i][3]};
+            }
+        }
+    };
+
+    // decays of a step, by one wave per head (its last): lane = position
+    const bool dwave = w == WPH - 1;
+    const float A2 = a.A[h] * LOG2E;
+    auto decays = [&](int par, float dtv) {
+        const float v = wave_scan(dtv * A2);
+        const float e0 = lane_value(v, 15), e1 = lane_value(v, 31), e2 = lane_value(v, 47);
+        const float last = lane_value(v, 63);
+        const float e = g == 0 ? e0 : g == 1 ? e1 : g == 2 ? e2 : last;   // last of the block of 16
+        a2s[par][hi][lane] = v;
+        dts[par][hi][lane] = dtv;
+        wst[par][hi][lane] = __builtin_amdgcn_exp2f(last - v) * dtv;
+        fss[par][hi][lane] = __builtin_amdgcn_exp2f(e - v) * dtv;
+    };
+
+    load_tiles(t_lo);
+    if (dwave)
+        decays(0, ndt);
+
+    // the entering state: zero, or the earlier segments' states carried here.
+    // S[pb][i]: dims 16 (PB w + pb) + c16, n = 16 i + 4 g .. +3.
+    f32x4 S[PB][8];
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            S[pb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (!STATE_ONLY && seg > 0) {
+        for (int sg = 0; sg < seg; ++sg) {
+            const size_t tile = ((size_t)b * (a.nseg - 1) + sg) * a.s.H + h;
+            const float dec = __builtin_amdgcn_exp2f(a.seg_decay[tile]);
+            const f32x4 *sp = (const f32x4 *)(a.seg_states + tile * (SP * SN)) + w * (PB * 8 * 64) + lane;
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    S[pb][i] = S[pb][i] * dec + sp[(pb * 8 + i) * 64];
+        }
+    }
+
+    if (!STATE_ONLY) {
+        // blocks above the diagonal that the within-step product reads
+        // (positions l of block 0 with s of block 1, and of 2 with 3)
+        for (int q = tid; q < NH * 64; q += NT) {
+            const int u = q & 1, r = 32 * ((q >> 5) & 1) + ((q >> 1) & 15), ch = 4 * ((q >> 5) & 1) + 2 + u;
+            *(u32x4 *)(mt + (q >> 6) * FM_BYTES + r * (FQ * 2) + ((ch ^ swz_fm(r)) * 16)) =
+                u32x4{0u, 0u, 0u, 0u};
+        }
+    }
+
+    // Per-lane LDS offsets of the operands within their tiles.  The chunk
+    // swizzles depend on the lane only, so another block or k-step is an XOR
+    // of its own chunk bits (and a constant for other rows).
+    //   transpose reads: rows 8 g + (c16 >> 2) (k-slots 0-3) and 4 further on,
+    //   four columns from 4 (c16 & 3) of the block
+    const int tr_row = 8 * g + (c16 >> 2);
+    uint32_t xtr = tr_row * (SP * 2) + ((2 * PB * w + ((c16 & 3) >> 1)) ^ swz_fx(tr_row)) * 16 + 8 * (c16 & 1);
+    uint32_t btr = tr_row * (SN * 2) + (((c16 & 3) >> 1) ^ swz_fb(tr_row)) * 16 + 8 * (c16 & 1);
+    //   row reads: row c16 of a block of 16
+    uint32_t crd = c16 * (SN * 2) + (g ^ swz_fc(c16)) * 16;
+    uint32_t brd = c16 * (SN * 2) + ((g >> 1) ^ swz_fb(c16)) * 16 + 8 * (g & 1);
+    uint32_t mrd = c16 * (FQ * 2) + (g ^ swz_fm(c16)) * 16;
+    uint32_t mwr = c16 * (FQ * 2) + ((g >> 1) ^ swz_fm(c16)) * 16 + 8 * (g & 1);
+    uint32_t xrd = c16 * (SP * 2) + ((2 * PB * w + (g >> 1)) ^ swz_fx(c16)) * 16 + 8 * (g & 1);
+
+    const float Dh = !STATE_ONLY && a.D ? a.D[h] : 0.f;
+    float seg_log = 0.f;
+    int par = 0;
+    store_tiles();
+    __syncthreads();
+    for (int t0 = t_lo;; t0 += FQ, par ^= 1) {
+        // (opaque once per step: the compiler would otherwise keep every
+        // address of a step in registers of its own and spill)
+        asm volatile("" : "+v"(btr), "+v"(crd), "+v"(brd), "+v"(mrd), "+v"(mwr), "+v"(xrd));
+        // the next step's tiles, waited for at the end of this one
+        load_tiles(t0 + FQ);
+
+        const unsigned char *xh = xt + hi * FX_BYTES;
+        const float *a2 = a2s[par][hi];
+        f32x4 y[PB][4];
+        if constexpr (!STATE_ONLY) {
+            // One pass over the C tile feeds both the entering-state term,
+            //   y^T[p][l] = sum_n S[p][n] C_l[n]   (scaled by exp(a_l) below),
+            // and column w4 of the blocks of (C B^T)^T, B_s . C_l for the 16
+            // positions s of block w4 (those above the diagonal are dropped).
+            f32x4 cbv[4];
+#pragma unroll
+            for (int lb = 0; lb < 4; ++lb) {
+                cbv[lb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb)
+                    y[pb][lb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                const unsigned char *bp = bt + w4 * (16 * SN * 2);
+                const u32x2 b0 = *(const u32x2 *)(bp + (brd ^ (64 * kk)));
+                const u32x2 b1 = *(const u32x2 *)(bp + (brd ^ (64 * kk + 32)));
+                const bf16x8 bv = __builtin_bit_cast(bf16x8, u32x4{b0[0], b0[1], b1[0], b1[1]});
+                u32x4 h4[PB], l4[PB];
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float v0 = S[pb][2 * kk + (q >> 1)][2 * (q & 1)];
+                        const float v1 = S[pb][2 * kk + (q >> 1)][2 * (q & 1) + 1];
+                        h4[pb][q] = pack_bf16(v0, v1);
+                        l4[pb][q] = pack_bf16(v0 - bf16_lo(h4[pb][q]), v1 - bf16_hi(h4[pb][q]));
+                    }
+#pragma unroll
+                for (int lb = 0; lb < 4; ++lb) {
+                    const bf16x8 cv = *(const bf16x8 *)(ct + lb * (16 * SN * 2) + (crd ^ (64 * kk)));
+                    cbv[lb] = mfma16(bv, cv, cbv[lb]);
+#pragma unroll
+                    for (int pb = 0; pb < PB; ++pb) {
+                        y[pb][lb] = mfma16(__builtin_bit_cast(bf16x8, h4[pb]), cv, y[pb][lb]);
+                        y[pb][lb] = mfma16(__builtin_bit_cast(bf16x8, l4[pb]), cv, y[pb][lb]);
+                    }
+                }
+            }
+            // The within-step weights (C_l . B_s) exp(a_l - a_s) dt_s.  Lane:
+            // position l = 16 lb + c16, positions s = 16 w4 + 4 g .. +3.
+            // Under the diagonal block s <= e < l for e the last position of
+            // block w4, and the weight is split there: fs[s] = exp(a_e - a_s)
+            // dt_s, times exp(a_l - a_e); both factors are finite.
+            const int s0 = 16 * w4 + 4 * g;
+#pragma unroll
+            for (int hh = 0; hh < NH; ++hh) {
+                const f32x4 f = *(const f32x4 *)&fss[par][hh][s0];
+                const float ae = a2s[par][hh][16 * w4 + 15];
+                unsigned char *mp = mt + hh * FM_BYTES + (mwr ^ (32 * w4));
+#pragma unroll
+                for (int lb = 0; lb < 4; ++lb) {
+                    if (lb < w4)
+                        continue;
+                    const float al = a2s[par][hh][16 * lb + c16];
+                    f32x4 m;
+                    if (lb == w4) {
+                        const f32x4 as = *(const f32x4 *)&a2s[par][hh][s0];
+                        const f32x4 ds = *(const f32x4 *)&dts[par][hh][s0];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const float e = cbv[lb][r] * (__builtin_amdgcn_exp2f(al - as[r]) * ds[r]);
+                            m[r] = 4 * g + r <= c16 ? e : 0.f;
+                        }
+                    } else {
+                        m = cbv[lb] * f * __builtin_amdgcn_exp2f(al - ae);
+                    }
+                    *(u32x2 *)(mp + lb * (16 * FQ * 2)) = u32x2{pack_bf16(m[0], m[1]), pack_bf16(m[2], m[3])};
+                }
+            }
+            // the decay to each position and the skip term
+#pragma unroll
+            for (int lb = 0; lb < 4; ++lb) {
+                const float e = __builtin_amdgcn_exp2f(a2[16 * lb + c16]);
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) {
+                    const u32x2 xv = *(const u32x2 *)(xh + (xrd ^ (32 * pb)) + lb * (16 * SP * 2));
+                    f32x4 &o = y[pb][lb];
+                    o[0] = o[0] * e + Dh * bf16_lo(xv[0]);
+                    o[1] = o[1] * e + Dh * bf16_hi(xv[0]);
+                    o[2] = o[2] * e + Dh * bf16_lo(xv[1]);
+                    o[3] = o[3] * e + Dh * bf16_hi(xv[1]);
+                }
+            }
+        }
+        bf16x8 xa[PB][2];
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                const unsigned char *xp = xh + (xtr ^ (32 * pb)) + ks * 32 * SP * 2;
+                xa[pb][ks] = tr_operand16(xp, xp + 4 * SP * 2);
+            }
+
+        // S^T[n][p] = exp(a_last) S^T + sum_l B_l[n] (w_l x_l[p])
+        const float last = a2[FQ - 1];
+        seg_log += last;
+        const float dec = __builtin_amdgcn_exp2f(last);
+        bf16x8 wx[PB][2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const f32x4 w0 = *(const f32x4 *)&wst[par][hi][32 * ks + 8 * g];
+            const f32x4 w1 = *(const f32x4 *)&wst[par][hi][32 * ks + 8 * g + 4];
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb) {
+                const u32x4 v = __builtin_bit_cast(u32x4, xa[pb][ks]);
+                wx[pb][ks] = __builtin_bit_cast(
+                    bf16x8, u32x4{pack_bf16(bf16_lo(v[0]) * w0[0], bf16_hi(v[0]) * w0[1]),
+                                  pack_bf16(bf16_lo(v[1]) * w0[2], bf16_hi(v[1]) * w0[3]),
+                                  pack_bf16(bf16_lo(v[2]) * w1[0], bf16_hi(v[2]) * w1[1]),
+                                  pack_bf16(bf16_lo(v[3]) * w1[2], bf16_hi(v[3]) * w1[3])});
+            }
+        }
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                S[pb][i] *= dec;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                // (rows 4 further on have the swizzle's low bit flipped)
+                const unsigned char *bp = bt + ks * (32 * SN * 2);
+                const bf16x8 bv = tr_operand16(bp + (btr ^ (32 * i)), bp + (btr ^ (32 * i + 16)) + 4 * SN * 2);
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb)
+                    S[pb][i] = mfma16(bv, wx[pb][ks], S[pb][i]);
+            }
+        if (dwave)
+            decays(par ^ 1, ndt);
+        __syncthreads();   // the weight tiles are complete, the others read
+
+        if constexpr (!STATE_ONLY) {
+            // (rows past L fall outside the buffer's range and are dropped)
+            const brsrc_t ry = range_rsrc(a.out + (size_t)b * L * xrow + (size_t)h * SP, t0, L,
+                                          xrow * 4, h * (SP * 4));
+#pragma unroll
+            for (int lb = 0; lb < 4; ++lb) {
+#pragma unroll
+                for (int ks = 0; ks <= lb / 2; ++ks) {
+                    const bf16x8 mv =
+                        *(const bf16x8 *)(mt + hi * FM_BYTES + lb * (16 * FQ * 2) + (mrd ^ (64 * ks)));
+#pragma unroll
+                    for (int pb = 0; pb < PB; ++pb)
+                        y[pb][lb] = mfma16(xa[pb][ks], mv, y[pb][lb]);
+                }
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb)
+                    buf_store<STREAM>(ry, ygo + lb * 16 * ypitch + pb * 64, y[pb][lb]);
+            }
+        }
+        if (t0 + FQ >= t_hi)
+            break;
+        store_tiles();
+        __syncthreads();   // the next step's tiles are complete, the weights read
+    }
+
+    if (STATE_ONLY) {
+        const size_t tile = ((size_t)b * (a.nseg - 1) + seg) * a.s.H + h;
+        f32x4 *sp = (f32x4 *)(a.seg_states + tile * (SP * SN)) + w * (PB * 8 * 64) + lane;
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                sp[(pb * 8 + i) * 64] = S[pb][i];
+        if (w == 0 && lane == 0)
+            a.seg_decay[tile] = seg_log;
+    } else if (a.final_states && seg == a.nseg - 1) {
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) {
+            float *f = a.final_states + (((size_t)b * a.s.H + h) * SP + 16 * (PB * w + pb) + c16) * SN + 4 * g;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                *(f32x4 *)(f + 16 * i) = S[pb][i];
+        }
+    }
+}
+
 bool misaligned(const void *p) { return ((uintptr_t)p & 15u) != 0; }
 
 bool overlaps(const void *p, size_t pn, const void *q, size_t qn)
@@ -689,6 +1163,39 @@ ta_status check_shape(int batch, int seqlen, int nheads, int ngroups, int headdi
     s.nc = (int)nc;
     s.hpg = nheads / ngroups;
     return TA_OK;
+}
+
+// Segments of the sequence that ssd_forward runs in parallel (1: one walk per
+// head from the first position to the last), and the steps in each.
+constexpr int MAX_SEGMENTS = 64;
+constexpr int SSD_FORWARD_MAX_HEADS = 1 << 17;   // 64 rows of x or y stay under 2^32 bytes
+
+void segment_shape(int seqlen, int num_segments, int *seg_steps, int *nseg)
+{
+    const int steps = (int)(((int64_t)seqlen + FQ - 1) / FQ);
+    *seg_steps = (steps + num_segments - 1) / num_segments;
+    *nseg = (steps + *seg_steps - 1) / *seg_steps;
+}
+
+size_t forward_ws_bytes(int batch, int nheads, int nseg)
+{
+    return (size_t)batch * (nseg - 1) * nheads * (SP * SN + 1) * 4;
+}
+
+template <int NH, bool STREAM>
+hipError_t launch_forward(FwdArgs &a, hipStream_t s)
+{
+    const int hgs = a.s.H / NH;
+    if (a.nseg > 1) {
+        a.n_wg = a.s.B * (a.nseg - 1) * hgs;
+        hipLaunchKernelGGL((ssd_forward_kernel<NH, true, false>), dim3(a.n_wg), dim3(NT), 0, s, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
+    a.n_wg = a.s.B * a.nseg * hgs;
+    hipLaunchKernelGGL((ssd_forward_kernel<NH, false, STREAM>), dim3(a.n_wg), dim3(NT), 0, s, a);
+    return hipGetLastError();
 }
 
 ta_status launched(hipError_t e) { return e == hipSuccess ? TA_OK : TA_ERR_LAUNCH; }
@@ -821,6 +1328,99 @@ ta_status ssd_state_passing(const float *states, const float *dt, const float *A
     PassArgs a{s, states, dt, A, prev_states, final_states};
     hipLaunchKernelGGL(state_passing_kernel, dim3(s.B * s.H * 4), dim3(NT), 0, (hipStream_t)stream, a);
     return launched(hipGetLastError());
+}
+
+ta_status ssd_forward(const void *x, const void *Bm, const void *Cm, const float *dt, const float *A,
+                      const float *D, float *out, float *final_states, int batch, int seqlen,
+                      int nheads, int ngroups, int headdim, int dstate, int num_segments,
+                      void *workspace, size_t workspace_bytes, void *stream)
+{
+    if (!x || !Bm || !Cm || !dt || !A || !out)
+        return TA_ERR_NULL_POINTER;
+    SsdShape s;
+    const ta_status st = check_shape(batch, seqlen, nheads, ngroups, headdim, dstate, SQ, s);
+    if (st != TA_OK)
+        return st;
+    // (32-bit offsets within a step's rows, 32-bit positions and grid)
+    if (num_segments < 1 || num_segments > MAX_SEGMENTS || nheads > SSD_FORWARD_MAX_HEADS ||
+        seqlen > (1 << 30) || (int64_t)batch * nheads * num_segments >= (1ll << 31))
+        return TA_ERR_INVALID_SHAPE;
+    if (misaligned(x) || misaligned(Bm) || misaligned(Cm) || misaligned(out) ||
+        misaligned(final_states) || ((uintptr_t)dt & 3) || ((uintptr_t)A & 3) || ((uintptr_t)D & 3))
+        return TA_ERR_MISALIGNED;
+    FwdArgs a;
+    a.s = s;
+    segment_shape(seqlen, num_segments, &a.seg_steps, &a.nseg);
+    const size_t nx = (size_t)batch * seqlen * nheads * SP;
+    const size_t nbc = (size_t)batch * seqlen * ngroups * SN * 2;
+    const size_t nf = final_states ? (size_t)batch * nheads * SP * SN * 4 : 0;
+    const size_t nws = forward_ws_bytes(batch, nheads, a.nseg);
+    if (nws && (!workspace || workspace_bytes < nws))
+        return TA_ERR_WORKSPACE;
+    if (nws && misaligned(workspace))
+        return TA_ERR_MISALIGNED;
+    const void *ins[] = {x, Bm, Cm, dt, A, D};
+    const size_t in_bytes[] = {nx * 2, nbc, nbc, (size_t)batch * seqlen * nheads * 4,
+                               (size_t)nheads * 4, D ? (size_t)nheads * 4 : 0};
+    for (int i = 0; i < 6; ++i)
+        if (overlaps(out, nx * 4, ins[i], in_bytes[i]) || overlaps(final_states, nf, ins[i], in_bytes[i]) ||
+            (nws && overlaps(workspace, nws, ins[i], in_bytes[i])))
+            return TA_ERR_ALIASING;
+    if (overlaps(out, nx * 4, final_states, nf) ||
+        (nws && (overlaps(workspace, nws, out, nx * 4) || overlaps(workspace, nws, final_states, nf))))
+        return TA_ERR_ALIASING;
+    a.x = (const uint16_t *)x;
+    a.Bm = (const uint16_t *)Bm;
+    a.Cm = (const uint16_t *)Cm;
+    a.dt = dt;
+    a.A = A;
+    a.D = D;
+    a.out = out;
+    a.final_states = final_states;
+    a.seg_states = (float *)workspace;
+    a.seg_decay = nws ? a.seg_states + (size_t)batch * (a.nseg - 1) * nheads * (SP * SN) : nullptr;
+    const bool strm = nx * 2 + nx * 4 > STREAM_BYTES;
+    // Two heads per workgroup share the B and C tiles and their product, once
+    // there are enough heads for a workgroup per CU (H=64 L=2048, one | two:
+    // B=4 88 | 140 us, B=8 166 | 153, B=16 357 | 246, B=64 1305 | 960).
+    const bool two = s.hpg % 2 == 0 && (int64_t)s.B * s.H >= 512;
+    const hipStream_t hs = (hipStream_t)stream;
+    const hipError_t e = two ? (strm ? launch_forward<2, true>(a, hs) : launch_forward<2, false>(a, hs))
+                             : (strm ? launch_forward<1, true>(a, hs) : launch_forward<1, false>(a, hs));
+    return launched(e);
+}
+
+ta_status ssd_forward_workspace_bytes(int batch, int seqlen, int nheads, int num_segments, size_t *bytes)
+{
+    if (!bytes)
+        return TA_ERR_NULL_POINTER;
+    if (batch < 1 || seqlen < 1 || nheads < 1 || num_segments < 1 || num_segments > MAX_SEGMENTS)
+        return TA_ERR_INVALID_SHAPE;
+    int seg_steps, nseg;
+    segment_shape(seqlen, num_segments, &seg_steps, &nseg);
+    *bytes = forward_ws_bytes(batch, nheads, nseg);
+    return TA_OK;
+}
+
+ta_status ssd_segment_heuristic(int batch, int seqlen, int nheads, int *num_segments)
+{
+    if (!num_segments)
+        return TA_ERR_NULL_POINTER;
+    if (batch < 1 || seqlen < 1 || nheads < 1)
+        return TA_ERR_INVALID_SHAPE;
+    // One-head workgroups, two per CU, and at least four steps per segment:
+    // every segment costs a second walk without C and y, and its state is
+    // read by all later segments (H=64, us by segment count: B=1 L=1000 1: 46,
+    // 2: 41, 4: 31, 8: 38; B=1 L=2048 1: 87, 4: 45, 8: 46, 16: 80; B=1 L=8192
+    // 1: 330, 4: 137, 8: 102, 16: 128).  From 256 heads on one walk per head
+    // is as fast (B=4 L=2048 1: 88, 2: 90, 4: 90).
+    const int64_t heads = (int64_t)batch * nheads;
+    const int steps = (int)(((int64_t)seqlen + FQ - 1) / FQ);
+    int n = heads >= 256 ? 1 : (int)(512 / heads);
+    n = n < MAX_SEGMENTS ? n : MAX_SEGMENTS;
+    n = n < steps / 4 ? n : steps / 4;
+    *num_segments = n < 1 ? 1 : n;
+    return TA_OK;
 }
 
 }  // extern "C"

@@ -76,6 +76,12 @@ def lib():
     L.ssd_bmm_chunk.argtypes = [p, p, p] + [i] * 5 + [p]
     L.ssd_chunk_scan.restype = i
     L.ssd_chunk_scan.argtypes = [p] * 8 + [i] * 7 + [p]
+    L.ssd_forward.restype = i
+    L.ssd_forward.argtypes = [p] * 8 + [i] * 7 + [p, ctypes.c_size_t, p]
+    L.ssd_forward_workspace_bytes.restype = i
+    L.ssd_forward_workspace_bytes.argtypes = [i] * 4 + [ctypes.POINTER(ctypes.c_size_t)]
+    L.ssd_segment_heuristic.restype = i
+    L.ssd_segment_heuristic.argtypes = [i] * 3 + [ctypes.POINTER(i)]
     L.ta_schedule.restype = i
     L.ta_schedule.argtypes = [i, i, i, i, i, ctypes.POINTER(i), ctypes.POINTER(i)]
     L.ta_tile_shape.restype = i
@@ -566,10 +572,53 @@ def ssd_chunk_scan(x, Cm, cb, dt, A, prev_states, D=None, out=None, stream=None)
     return out
 
 
-def ssd_forward(x, dt, A, Bm, Cm, D=None, stream=None):
-    """The four SSD functions chained on the GPU: (y [B, L, H, P], final
-    states [B, H, P, N])."""
-    states = ssd_chunk_state(x, Bm, dt, A, stream=stream)
-    prev, final = ssd_state_passing(states, dt, A, stream=stream)
-    cb = ssd_bmm_chunk(Cm, Bm, stream=stream)
-    return ssd_chunk_scan(x, Cm, cb, dt, A, prev, D, stream=stream), final
+def ssd_segment_heuristic(batch: int, seqlen: int, nheads: int) -> int:
+    n = ctypes.c_int()
+    _ssd_raise(lib().ssd_segment_heuristic(batch, seqlen, nheads, ctypes.byref(n)))
+    return n.value
+
+
+def ssd_forward_workspace_bytes(batch: int, seqlen: int, nheads: int, num_segments: int) -> int:
+    n = ctypes.c_size_t()
+    _ssd_raise(lib().ssd_forward_workspace_bytes(batch, seqlen, nheads, num_segments,
+                                                 ctypes.byref(n)))
+    return n.value
+
+
+def ssd_forward(x, dt, A, Bm, Cm, D=None, stream=None, num_segments: int | None = None):
+    """(y [B, L, H, P], final states [B, H, P, N]) of the Mamba-2 recurrence:
+    what the four SSD functions give chained, in one call.  ``num_segments``
+    (default ssd_segment_heuristic) is the number of pieces of the sequence
+    that run in parallel."""
+    import torch
+
+    Bsz, L, H, G, P, N, _ = _ssd_dims(x, Bm)
+    _ssd_check("x", x, torch.bfloat16, (Bsz, L, H, P))
+    _ssd_check("Bm", Bm, torch.bfloat16, (Bsz, L, G, N))
+    _ssd_check("dt", dt, torch.float32, (Bsz, L, H))
+    _ssd_check("A", A, torch.float32, (H,))
+    _ssd_check("Cm", Cm, torch.bfloat16, (Bsz, L, G, N))
+    if D is not None:
+        _ssd_check("D", D, torch.float32, (H,))
+    if H > 1 << 17 or L > 1 << 30:   # outside the one-pass call: the functions chained
+        states = ssd_chunk_state(x, Bm, dt, A, stream=stream)
+        prev, final = ssd_state_passing(states, dt, A, stream=stream)
+        cb = ssd_bmm_chunk(Cm, Bm, stream=stream)
+        return ssd_chunk_scan(x, Cm, cb, dt, A, prev, D, stream=stream), final
+    stream = stream or torch.cuda.current_stream(x.device)
+    if num_segments is None:
+        num_segments = ssd_segment_heuristic(Bsz, L, H)
+    need = ssd_forward_workspace_bytes(Bsz, L, H, num_segments)
+    out = torch.empty((Bsz, L, H, P), dtype=torch.float32, device=x.device)
+    final = torch.empty((Bsz, H, P, N), dtype=torch.float32, device=x.device)
+    ws = None
+    if need:
+        ws = torch.empty(need, dtype=torch.uint8, device=x.device)
+        ws.record_stream(stream)   # as in attn_fwd_split
+    with _one_device(x, Bm, Cm, dt, A, D, out):
+        _ssd_raise(lib().ssd_forward(x.data_ptr(), Bm.data_ptr(), Cm.data_ptr(), dt.data_ptr(),
+                                     A.data_ptr(), D.data_ptr() if D is not None else None,
+                                     out.data_ptr(), final.data_ptr(), Bsz, L, H, G, P, N,
+                                     num_segments, ws.data_ptr() if need else None, need,
+                                     stream.cuda_stream))
+    return out, final

@@ -375,3 +375,36 @@ def test_ssd_bmm_and_passing_validation_before_any_hip_call():
     assert L.ssd_state_passing(SST, SDT, SA, SOUT, None, 1, 300, 4, 32, 128, 256, None) == 3
     assert L.ssd_state_passing(SST, SDT, SA, SST + 1024, None, 1, 300, 4, 64, 128, 256, None) == 6
     assert L.ssd_state_passing(SST, SDT, SA, SOUT, SOUT + 64, 1, 300, 4, 64, 128, 256, None) == 6
+
+
+@no_gpu
+def test_ssd_forward_validation_before_any_hip_call():
+    ok = dict(x=SX, Bm=SB, Cm=SC, dt=SDT, A=SA, D=SD, out=SOUT, fin=SST, B=1, L=300, H=4, G=2, P=64,
+              N=128, seg=2, ws=SCB, ws_bytes=1 << 20)
+
+    def rc(**change):
+        a = dict(ok, **change)
+        return ta.lib().ssd_forward(a["x"], a["Bm"], a["Cm"], a["dt"], a["A"], a["D"], a["out"], a["fin"],
+                                    a["B"], a["L"], a["H"], a["G"], a["P"], a["N"], a["seg"], a["ws"],
+                                    a["ws_bytes"], None)
+
+    for change, status in [
+            (dict(x=0), 1), (dict(out=0), 1), (dict(L=0), 2), (dict(H=3), 2), (dict(seg=0), 2),
+            (dict(seg=65), 2), (dict(H=1 << 18), 2), (dict(P=32), 3), (dict(N=64), 3),
+            (dict(x=SX + 8), 4), (dict(fin=SST + 4), 4), (dict(dt=SDT + 2), 4), (dict(ws=SCB + 4), 4),
+            (dict(out=SX + 1024), 6), (dict(fin=SOUT + 64), 6), (dict(ws=SX), 6), (dict(ws=SOUT), 6),
+            (dict(ws=0), 8), (dict(ws_bytes=1000), 8)]:
+        assert rc(**change) == status, change
+
+
+def test_ssd_segments():
+    # steps of 64: 300 positions are 5 steps; trailing empty segments are dropped
+    for seg, used in [(1, 1), (2, 2), (3, 3), (4, 3), (64, 5)]:
+        assert ta.ssd_forward_workspace_bytes(2, 300, 6, seg) == 2 * (used - 1) * 6 * (64 * 128 + 1) * 4
+    for B, L, H in [(1, 1, 1), (1, 1000, 64), (1, 8192, 64), (1, 1 << 20, 1), (4, 2048, 64), (64, 8192, 64)]:
+        n = ta.ssd_segment_heuristic(B, L, H)
+        assert 1 <= n <= 64
+        assert n == 1 or (B * H < 256 and B * H * n <= 512 and -(-L // 64) >= 4 * n)
+    for bad in [(0, 1, 1), (1, 0, 1), (1, 1, 0)]:
+        with pytest.raises(ta.TileAttnError):
+            ta.ssd_segment_heuristic(*bad)

@@ -233,3 +233,42 @@ def test_repeatable_and_stream(ta):
         y3 = ta.ssd_chunk_scan(*a, stream=s)
     s.synchronize()
     assert torch.equal(y1, y2) and torch.equal(y1, y3)
+
+
+@pytest.mark.parametrize("shape,segments", [
+    ((1, 1, 1, 1), 1),         # one position
+    ((1, 64, 2, 2), 1),        # exactly one step
+    ((2, 65, 3, 1), 2),        # one position into the second step, odd heads
+    ((1, 300, 4, 2), 3),       # ragged last step, segments of two steps (the last short)
+    ((1, 1000, 6, 3), 16),     # a segment per step
+    ((2, 200, 256, 2), 1),     # two heads per workgroup
+    ((2, 200, 256, 2), 2),     # ... with segments
+    ((1, 70, 513, 171), 1),    # groups of three heads: one per workgroup
+], ids=str)
+def test_forward_one_pass(ta, shape, segments):
+    """ssd_forward's kernel (steps of 64 positions, segments) against the
+    oracle's chain and the four chained functions, with and without the skip
+    term; the same bounds as the chain, whose roundings it has one of."""
+    print(f"ssd_forward {shape} segments={segments}", flush=True)
+    w, inp = problem(shape, seed=41 + sum(shape))
+    dx, dB, dC = dev_bf16(inp["x"]), dev_bf16(inp["Bm"]), dev_bf16(inp["Cm"])
+    ddt, dA, dD = dev_f32(inp["dt"]), dev_f32(inp["A"]), dev_f32(inp["D"])
+    y, final = ta.ssd_forward(dx, ddt, dA, dB, dC, dD, num_segments=segments)
+    y0, final0 = ta.ssd_forward(dx, ddt, dA, dB, dC, None, num_segments=segments)
+    states = ta.ssd_chunk_state(dx, dB, ddt, dA)
+    prev, cfinal = ta.ssd_state_passing(states, ddt, dA)
+    cy = ta.ssd_chunk_scan(dx, dC, ta.ssd_bmm_chunk(dC, dB), ddt, dA, prev, dD)
+    torch.cuda.synchronize()
+    assert torch.equal(final, final0)
+    ry, rf = ossd.ssd_forward(inp["x"], inp["dt"], inp["A"], inp["Bm"], inp["Cm"], inp["D"], Q)
+    scale = chained_scale(inp)
+    check(f"one pass y {shape}", y.cpu().numpy(), ry, scale, bound=2.0 ** -6, rms=2.0 ** -8)
+    # without the skip term: y less D x, to fp32 rounding of that sum
+    skip = dD[None, None, :, None] * dx.float()
+    assert float((y - y0 - skip).abs().max()) <= 2.0 ** -20 * float(y.abs().max() + skip.abs().max())
+    fs = ossd.state_passing(ossd.chunk_state_abs(inp["x"], inp["Bm"], inp["dt"], inp["A"], Q),
+                            inp["dt"], inp["A"], Q)[1]
+    check(f"one pass final {shape}", final.cpu().numpy(), rf, np.maximum(fs, 1e-30))
+    # both paths are within the bound of the same value
+    assert float(((y - cy).abs().cpu().numpy() / np.maximum(scale, 1e-30)).max()) <= 2.0 ** -5
+    assert float(((final - cfinal).abs().cpu().numpy() / np.maximum(fs, 1e-30)).max()) <= 2.0 ** -6
