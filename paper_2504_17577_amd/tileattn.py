@@ -53,6 +53,8 @@ def lib():
     L.ta_split_workspace_bytes.argtypes = [i, i, i, i, i, ctypes.POINTER(ctypes.c_size_t)]
     L.ta_split_heuristic.restype = i
     L.ta_split_heuristic.argtypes = [i, i, i, i, i, i, i, ctypes.POINTER(i)]
+    L.ta_split_plan.restype = i
+    L.ta_split_plan.argtypes = L.ta_split_heuristic.argtypes
     L.mla_decode.restype = i
     L.mla_decode.argtypes = [p, p, p, p, p, p, i, i, i, i, i, i, ctypes.c_float, i, p,
                              ctypes.c_size_t, p]
@@ -130,6 +132,14 @@ def ta_split_workspace_bytes(B: int, Hq: int, Sq: int, D: int, num_splits: int) 
 def ta_split_heuristic(B: int, Hq: int, Hkv: int, Sq: int, Sk: int, D: int, causal: bool) -> int:
     n = ctypes.c_int()
     rc = lib().ta_split_heuristic(B, Hq, Hkv, Sq, Sk, D, int(bool(causal)), ctypes.byref(n))
+    if rc != TA_OK:
+        raise TileAttnError(rc, ta_status_string(rc))
+    return n.value
+
+
+def ta_split_plan(B: int, Hq: int, Hkv: int, Sq: int, Sk: int, D: int, causal: bool) -> int:
+    n = ctypes.c_int()
+    rc = lib().ta_split_plan(B, Hq, Hkv, Sq, Sk, D, int(bool(causal)), ctypes.byref(n))
     if rc != TA_OK:
         raise TileAttnError(rc, ta_status_string(rc))
     return n.value
@@ -229,8 +239,8 @@ def attn_fwd_split(q, k, v, causal: bool = False, scale: float | None = None,
                    num_splits: int | None = None, out=None, lse=None, workspace=None,
                    out_dtype=None, stream=None):
     """attn_fwd with the key range split over ``num_splits`` workgroups per
-    query tile (default: ta_split_heuristic) and the partial results merged
-    by a second kernel.  ``workspace`` is a uint8 GPU tensor of at least
+    query tile (default: ta_split_heuristic with a given workspace, else
+    ta_split_plan) and the partial results merged by a second kernel.  ``workspace`` is a uint8 GPU tensor of at least
     ta_split_workspace_bytes(...) bytes (allocated here if None); it must
     stay alive until the launch has finished on ``stream``.  ``out_dtype``
     is torch.float32 (default) or torch.bfloat16."""
@@ -242,7 +252,8 @@ def attn_fwd_split(q, k, v, causal: bool = False, scale: float | None = None,
     B, Hq, Sq, D = q.shape
     Hkv, Sk = k.shape[1], k.shape[2]
     if num_splits is None:
-        num_splits = ta_split_heuristic(B, Hq, Hkv, Sq, Sk, D, causal)
+        plan = ta_split_plan if workspace is None else ta_split_heuristic
+        num_splits = plan(B, Hq, Hkv, Sq, Sk, D, causal)
     need = ta_split_workspace_bytes(B, Hq, Sq, D, num_splits)
     if stream is None:
         stream = torch.cuda.current_stream(q.device)

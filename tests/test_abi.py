@@ -194,6 +194,20 @@ def test_split_heuristic_properties(shape):
         assert n_kv // 32 <= 1                    # only when the keys are too short to split
 
 
+@pytest.mark.parametrize("shape", [
+    (8, 32, 8, 1, 8191, 128, False), (1, 32, 8, 1, 8191, 64, False), (1, 1, 1, 1, 100000, 64, True),
+    (300, 8, 8, 1, 4096, 128, False), (1, 16, 1, 1, 511, 128, False), (1, 2, 1, 8, 1 << 20, 64, True),
+    (1, 32, 8, 512, 8192, 128, True), (1, 17, 1, 1, 8192, 128, False),
+])
+def test_split_plan_properties(shape):
+    B, Hq, Hkv, Sq, Sk, D, causal = shape
+    n = ta.ta_split_plan(*shape)
+    if Hq // Hkv * Sq > 16:                      # the tiled kernel
+        assert n == ta.ta_split_heuristic(*shape)
+    else:                                        # one workgroup per CU, 512 keys per split
+        assert n == max(1, min(256 // (B * Hkv), Sk // 512, 128))
+
+
 # mla_decode: argument errors before any HIP call (fake pointers)
 MQ, MQP, MKV, MKP, MO, ML, MWS = (0x10000000, 0x18000000, 0x20000000, 0x30000000, 0x40000000,
                                   0x50000000, 0x60000000)

@@ -154,3 +154,33 @@ def test_split_side_stream_with_its_own_workspace(ta):
     del junk
     assert torch.equal(o, o_ref) and torch.equal(lse, l_ref)
     assert torch.equal(mo, mo_ref) and torch.equal(ml, ml_ref)
+
+
+@pytest.mark.parametrize("case", [
+    # (B, Hq, Hkv, Sq, Sk, D, causal, splits): up to 16 query rows per K/V head
+    (1, 1, 1, 1, 1, 128, True, 1),          # one key
+    (2, 2, 1, 1, 31, 64, False, 1),         # less than a tile
+    (1, 16, 1, 1, 257, 128, False, 1),      # all 16 rows, one key past eight waves' tiles
+    (2, 8, 4, 8, 300, 64, True, 1),         # 16 rows over two heads, diagonal in the last tile
+    (1, 3, 3, 16, 16, 128, True, 1),        # square causal: rows see 1 .. 16 keys
+    (1, 10, 2, 3, 1000, 128, True, 1),      # 15 rows
+    (3, 8, 2, 1, 1000, 64, False, 3),       # splits of whole tiles, ragged end
+    (1, 4, 1, 4, 130, 128, True, 3),        # last split seen by some rows only
+    (2, 32, 8, 1, 4099, 128, False, 16),
+], ids=str)
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16], ids=["fp32", "bf16"])
+def test_decode_rows_against_oracle(ta, case, out_dtype):
+    B, Hq, Hkv, Sq, Sk, D, causal, splits = case
+    print(f"decode case {case} {out_dtype}", flush=True)
+    q, k, v = gen.random_problem(B, Hq, Hkv, Sq, Sk, D, seed=17)
+    o, lse = run_split(ta, q, k, v, causal, D ** -0.5, splits, out_dtype=out_dtype)
+    ro, rl = oracle.attn_fwd(q, k, v, causal, D ** -0.5)
+    o, lse = o.float().cpu().numpy(), lse.cpu().numpy()
+    assert np.isfinite(o).all() and np.isfinite(lse).all()
+    eo, el = float(np.abs(o - ro).max()), float(np.abs(lse - rl).max())
+    print(f"  max|dO|={eo:.3e} max|dLSE|={el:.3e}", flush=True)
+    assert eo <= O_TOL and el <= LSE_TOL
+    # scale 0: every visible key weighs the same
+    _, lse0 = run_split(ta, q, k, v, causal, 0.0, splits, out_dtype=out_dtype)
+    seen = np.array([min(Sk, i + 1 + Sk - Sq) if causal else Sk for i in range(Sq)])
+    assert float(np.abs(lse0.cpu().numpy() - np.log(seen)).max()) <= 1e-5
