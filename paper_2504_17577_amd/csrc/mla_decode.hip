@@ -10,9 +10,9 @@
 // cache serving again as the value).  The design is this library's own for
 // CDNA4:
 //
-//  * One workgroup of eight wave64s (two per SIMD) owns HB = 128 query
-//    heads of one latent head of one batch element, and one range of cache
-//    tiles (a key split); wave w owns 16 of the heads.  S^T = K Q^T with
+//  * One workgroup of eight wave64s (two per SIMD) owns up to HB = 128 query
+//    heads of one latent head of one batch element (fewer in small grids),
+//    and one range of cache tiles (a key split); wave w owns 16 of the heads.  S^T = K Q^T with
 //    v_mfma_f32_16x16x32_bf16 over the full 576-wide contraction (A = 16
 //    cache rows from LDS, B = the query of the wave's 16 heads, held in
 //    registers for the whole kernel: 72 per lane).  In the 16x16 accumulator
@@ -102,6 +102,7 @@ struct MArgs {
     size_t o_split, l_split;  // element strides between splits
     int B, H, Hkv, Skv;
     int g;                    // H / Hkv query heads per latent head
+    int hb;                   // query heads per workgroup (16 .. 128)
     int n_hblk;               // workgroups over the heads of one latent head
     int n_split, split_tiles;
     int n_wg;
@@ -204,12 +205,14 @@ struct Mla {
         va0 = row * (DL * 2) + 16 * (((hc & 3) >> 1) ^ lat_swz(row)) + 8 * (hc & 1);
     }
 
-    // DMA cache tile j (positions j*BN ..) into `stage`, with non-temporal
-    // loads: each tile is read by this workgroup only, once (measured 1-2.5 %
-    // faster on mla_b64_s8k and mla_b128_s4k, the same output).  Each buffer
+    // DMA cache tile j (positions j*BN ..) into `stage`.  ONCE: with
+    // non-temporal loads, where each tile is read by this workgroup only
+    // (measured 1-2.5 % faster on mla_b64_s8k and mla_b128_s4k, the same
+    // output).  Each buffer
     // resource starts at the tile and ends after its last valid row; a row
     // past Skv re-reads the last valid row (its scores are masked and its
     // weights zero), so no lane addresses outside the cache.
+    template <bool ONCE>
     __device__ __forceinline__ void dma_tile(int j, unsigned char *stage) const
     {
         const int valid = min(BN, a.Skv - j * BN);
@@ -221,7 +224,7 @@ struct Mla {
         if (valid == BN) {
 #pragma unroll
             for (int i = 0; i < LAT_PER_THREAD; ++i)
-                tileattn_dma::dma16_soff<true>(lat_base + i * NT * 16, lat_off[i & 1],
+                tileattn_dma::dma16_soff<ONCE>(lat_base + i * NT * 16, lat_off[i & 1],
                                          16 * (i >> 1) * lat_pitch, rl);
         } else {
             const int last = valid - 1;
@@ -233,7 +236,7 @@ struct Mla {
                 const int src = row > last ? last : row;
                 const uint32_t o = lat_off[i & 1] + (uint32_t)((src - 8 * (i & 1) - wave_u) *
                                                                (int)lat_pitch);
-                tileattn_dma::dma16<true>(lat_base + i * NT * 16, o, rl);
+                tileattn_dma::dma16<ONCE>(lat_base + i * NT * 16, o, rl);
             }
         }
         if (rot_wave) {
@@ -242,7 +245,7 @@ struct Mla {
             // row 8w + l/8 is lane-dependent: clamp per lane
             const int row = 8 * (wave_u & 3) + lane / 8;
             const int shift = row > valid - 1 ? row - (valid - 1) : 0;
-            tileattn_dma::dma16<true>(tileattn_dma::lds_addr(stage + LAT_BYTES) + wave_u * 64 * 16,
+            tileattn_dma::dma16<ONCE>(tileattn_dma::lds_addr(stage + LAT_BYTES) + wave_u * 64 * 16,
                                 rot_off - (uint32_t)shift * rot_pitch, rr);
         }
     }
@@ -386,7 +389,7 @@ struct Mla {
     // t+2 goes into the stage of tile t-2; then the scores of tile t, the
     // P V of tile t-1 (weights pk, rows in stage (t-1) % 4) and the softmax
     // of tile t, whose weights replace pk.
-    template <bool MASKED, bool FIRST>
+    template <bool MASKED, bool FIRST, bool ONCE>
     __device__ __forceinline__ void step(int t, int n, int j_lo, unsigned char *ring,
                                          uint32_t (&pk)[4])
     {
@@ -396,7 +399,7 @@ struct Mla {
             wait_tiles<0>(rot_wave);
         __syncthreads();
         if (t + 2 < n)
-            dma_tile(j_lo + t + 2, ring + ((t + 2) % NST) * STAGE_BYTES);
+            dma_tile<ONCE>(j_lo + t + 2, ring + ((t + 2) % NST) * STAGE_BYTES);
         if (busy) {
             f32x4 s[2];
             mma<true, !FIRST>(ring + (t % NST) * STAGE_BYTES,
@@ -423,6 +426,7 @@ __device__ __forceinline__ void decode_wg(const MArgs &a, int bid, int &b, int &
     b = l / a.Hkv;
 }
 
+template <bool ONCE>
 __global__ __launch_bounds__(NT, 1) void mla_decode_kernel(MArgs args)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char ring[NST * STAGE_BYTES];
@@ -445,19 +449,20 @@ __global__ __launch_bounds__(NT, 1) void mla_decode_kernel(MArgs args)
     const int n = j_hi - j_lo;
 
     // this lane's head: local index within the latent head's group
-    const int h_loc = hblk * HB + k.wave_u * HW + k.hc;
-    const bool head_ok = h_loc < a.g;
+    const int h_loc = hblk * a.hb + k.wave_u * HW + k.hc;
+    const int h_end = min(a.g, (hblk + 1) * a.hb);   // past the workgroup's last head
+    const bool head_ok = h_loc < h_end;
     const int head = hk * a.g + min(h_loc, a.g - 1);
-    k.busy = hblk * HB + k.wave_u * HW < a.g;   // wave-uniform
+    k.busy = hblk * a.hb + k.wave_u * HW < h_end;   // wave-uniform
 
     k.kv_b = a.KV + ((size_t)b * a.Skv * a.Hkv + hk) * DL;
     k.kpe_b = a.Kpe + ((size_t)b * a.Skv * a.Hkv + hk) * DR;
     k.init_lanes();
 
     // prologue: the first two tiles in flight
-    k.dma_tile(j_lo, ring);
+    k.dma_tile<ONCE>(j_lo, ring);
     if (n > 1)
-        k.dma_tile(j_lo + 1, ring + STAGE_BYTES);
+        k.dma_tile<ONCE>(j_lo + 1, ring + STAGE_BYTES);
 
     // the query of the lane's head as the B operand: k-step kk holds dims
     // 32kk + 8gq .. +8 of [q | q_pe]
@@ -487,14 +492,14 @@ __global__ __launch_bounds__(NT, 1) void mla_decode_kernel(MArgs args)
     const int n_full = min(j_hi, a.Skv / BN) - j_lo;
     uint32_t pk[4];
     if (n_full > 0)
-        k.step<false, true>(0, n, j_lo, ring, pk);
+        k.step<false, true, ONCE>(0, n, j_lo, ring, pk);
     else
-        k.step<true, true>(0, n, j_lo, ring, pk);
+        k.step<true, true, ONCE>(0, n, j_lo, ring, pk);
     int t = 1;
     for (; t < n_full; ++t)
-        k.step<false, false>(t, n, j_lo, ring, pk);
+        k.step<false, false, ONCE>(t, n, j_lo, ring, pk);
     if (t < n)
-        k.step<true, false>(t, n, j_lo, ring, pk);
+        k.step<true, false, ONCE>(t, n, j_lo, ring, pk);
     // the last tile's P V
     {
         f32x4 s_unused[2];
@@ -628,7 +633,23 @@ ta_status mla_decode(const void *Q, const void *Q_pe, const void *KV, const void
         a.l_split = 0;
     }
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(mla_decode_kernel, dim3(a.n_wg), dim3(NT), 0, s, a);
+    // Fewer heads per workgroup (waves without heads only fetch tiles) while
+    // the grid still fits one workgroup per CU: every wave's reads of a tile
+    // pass through its CU's LDS, so a workgroup of 16 heads takes 0.9 us a
+    // tile where one of 128 takes 2.1, and its share of the queries and
+    // outputs is an eighth.  The head blocks of a split then read its tiles
+    // from their XCD's L2.  (us, 128 heads per workgroup -> this: B=1 H=128
+    // Skv=1 15 -> 8; B=4 Skv=1999 39 -> 26; B=1 Skv=8192 41 -> 29; B=16
+    // Skv=1999 46 -> 34; going on to two workgroups per CU: 34 -> 49.)
+    a.hb = HB;
+    while (a.hb > HW && (int64_t)B * Hkv * ((g + a.hb / 2 - 1) / (a.hb / 2)) * n_split <= MLA_TARGET_WG)
+        a.hb /= 2;
+    a.n_hblk = (g + a.hb - 1) / a.hb;
+    a.n_wg = B * Hkv * a.n_hblk * n_split;
+    if (a.n_hblk == 1)
+        hipLaunchKernelGGL(mla_decode_kernel<true>, dim3(a.n_wg), dim3(NT), 0, s, a);
+    else
+        hipLaunchKernelGGL(mla_decode_kernel<false>, dim3(a.n_wg), dim3(NT), 0, s, a);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && n_split > 1)
         e = tileattn_detail::launch_combine<DL, false>(Op, Lp, O, LSE, (int)rows, n_split, nq,

@@ -168,3 +168,22 @@ def test_mla_rejects_bad_arguments(ta):
     with pytest.raises(ta.TileAttnError) as e:
         ta.mla_decode(q2, qp2, kv2, kp2)
     assert e.value.status == 3
+
+
+@pytest.mark.parametrize("case", [
+    # (B, H, Hkv, Skv, splits): 256 workgroups allow 16, 32, 64 heads each, or
+    # the grid takes all 128
+    (1, 128, 1, 33, 1),       # 16 heads per workgroup
+    (1, 40, 1, 300, 2),       # 16, the last block half full
+    (2, 200, 2, 100, 3),      # 100 heads per latent head: seven blocks, the last of four
+    (40, 128, 1, 70, 2),      # 64
+    (33, 100, 1, 64, 2),      # 64: blocks of 64 and 36
+    (80, 128, 1, 40, 2),      # 128
+], ids=str)
+def test_mla_head_blocks(ta, case):
+    B, H, Hkv, Skv, splits = case
+    print(f"mla head blocks {case}", flush=True)
+    q, q_pe, kv, k_pe = gen.random_mla_problem(B, H, Hkv, Skv, seed=23)
+    o, lse = run(ta, q, q_pe, kv, k_pe, 576 ** -0.5, splits)
+    ro, rl = oracle.mla_decode(q, q_pe, kv, k_pe, 576 ** -0.5)
+    check(f"mla head blocks {case}", o, lse, ro, rl)
