@@ -233,6 +233,31 @@ ta_status gemm_bf16(const void *A, const void *B, void *C, int c_bf16, int M, in
                     void *stream);
 
 /*
+ * gemm_bf16_split — gemm_bf16 with the K steps of every tile of C split into
+ * num_splits ranges that separate workgroups sum, for products with too few
+ * 128 x 128 tiles of C to occupy every CU.
+ *
+ *   num_splits 1..64 (else TA_ERR_INVALID_SHAPE), at most K / 64 (else
+ *   TA_ERR_UNSUPPORTED); 1 runs gemm_bf16 and ignores the workspace; for
+ *   more, each range's fp32 product goes to `workspace` (device, 16-byte
+ *   aligned, at least num_splits * M * N * 4 bytes, owned by the caller, no
+ *   overlap with A, B or C; TA_ERR_WORKSPACE if NULL or smaller) and a second
+ *   kernel adds them in range order, rounding once if C is bf16
+ *   M % 128 == 0 then as well; other arguments and status codes as gemm_bf16
+ */
+ta_status gemm_bf16_split(const void *A, const void *B, void *C, int c_bf16, int M, int N, int K,
+                          int num_splits, void *workspace, size_t workspace_bytes, void *stream);
+
+/* Workspace bytes gemm_bf16_split needs: num_splits * M * N * 4 for
+ * num_splits > 1, 0 for 1.  No HIP call. */
+ta_status gemm_split_workspace_bytes(int M, int N, int num_splits, size_t *bytes);
+
+/* A split count for gemm_bf16_split: 1 unless splitting is estimated to be
+ * clearly faster (up to 256 tiles of 128 x 128, long K), with at most 512
+ * workgroups (tiles x splits).  No HIP call. */
+ta_status gemm_split_heuristic(int M, int N, int K, int *num_splits);
+
+/*
  * gemv_bf16_split — the matrix-vector product C[n] = sum_k A[k] B[k][n] of
  * gemm_bf16 with M == 1 (the paper's V0-V7 shapes, appendix table "Matrix
  * shapes in our benchmark"), with the K rows split into num_splits ranges

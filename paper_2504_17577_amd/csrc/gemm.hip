@@ -68,7 +68,10 @@ struct GArgs {
     void *C;
     int M, N, K;
     int tiles_n;     // N / BN
-    int n_wg;
+    int n_tiles;     // tiles of C
+    int n_split;     // K ranges per tile; with more than one, C is fp32
+                     // [n_split][M][N], one partial product per range
+    int n_wg;        // n_tiles * n_split
 };
 
 [[maybe_unused]] __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c)
@@ -178,7 +181,8 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(GArgs args)
     // XCD-contiguous logical tile index, row-major over the tiles of C
     const int per = a.n_wg / NXCD, rem = a.n_wg % NXCD;
     const int xcd = blockIdx.x % NXCD, idx = blockIdx.x / NXCD;
-    const int t = xcd * per + (xcd < rem ? xcd : rem) + idx;
+    const int ts = xcd * per + (xcd < rem ? xcd : rem) + idx;
+    const int t = ts % a.n_tiles, split = ts / a.n_tiles;
     // grouped order: GROUP_M consecutive logical tiles walk down a column of
     // tiles before moving right, so the workgroups resident on an XCD cover
     // a GROUP_M x (resident / GROUP_M) block of C and share its A and B
@@ -213,8 +217,13 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(GArgs args)
         b_off[i] = (uint32_t)r * a.N * 2 + 16 * (sc ^ b_swz<MF>(r));
     }
 
+    // this range's K steps (ranges of whole steps, as even as they go)
+    const int kt_all = a.K / BK;
+    const int kt_lo = (int)((int64_t)kt_all * split / a.n_split);
+    const int n_kt = (int)((int64_t)kt_all * (split + 1) / a.n_split) - kt_lo;
+
     auto dma = [&](int kt, unsigned char *as, unsigned char *bs) {
-        const int k0 = kt * BK;
+        const int k0 = (kt_lo + kt) * BK;
         const u32x4s ra = buffer_rsrc(a.A + (size_t)m0 * a.K + k0,
                                       (uint32_t)((BM - 1) * a.K + BK) * 2);
         const u32x4s rb = buffer_rsrc(a.B + (size_t)k0 * a.N + n0,
@@ -281,7 +290,6 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(GArgs args)
         }
     };
 
-    const int n_kt = a.K / BK;
     if constexpr (ST == 2) {
         dma(0, a0, b0);
         wait_dma_all();
@@ -373,6 +381,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(GArgs args)
 
     // epilogue: lane holds column wn + MF j + col, rows wm + MF i +
     // 8(r/4) + 4half + r%4 (MF = 32) or 4half + r (MF = 16) of the tile
+    const size_t c0 = CBF16 ? 0 : (size_t)split * a.M * a.N;
 #pragma unroll
     for (int i = 0; i < C::FM; ++i)
 #pragma unroll
@@ -385,7 +394,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(GArgs args)
                     ((uint16_t *)a.C)[(size_t)m * a.N + n] =
                         (uint16_t)pack_bf16(acc[i][j][r], 0.f);
                 else
-                    ((float *)a.C)[(size_t)m * a.N + n] = acc[i][j][r];
+                    ((float *)a.C)[c0 + (size_t)m * a.N + n] = acc[i][j][r];
             }
         }
 }
@@ -621,13 +630,40 @@ hipError_t launch(GArgs &a, bool c_bf16, hipStream_t s)
 {
     constexpr int MF = (BK / 32) % KS == 0 ? 16 : 32;
     a.tiles_n = a.N / BN;
-    a.n_wg = (a.M / BM) * a.tiles_n;
+    a.n_tiles = (a.M / BM) * a.tiles_n;
+    a.n_wg = a.n_tiles * a.n_split;
     if (c_bf16)
         hipLaunchKernelGGL((gemm_kernel<BM, BN, ST, KS, MF, true>), dim3(a.n_wg), dim3(NT), 0, s, a);
     else
         hipLaunchKernelGGL((gemm_kernel<BM, BN, ST, KS, MF, false>), dim3(a.n_wg), dim3(NT), 0, s, a);
     return hipGetLastError();
 }
+
+// C = W[0] + W[1] + ... + W[S-1], added in that order (fp32), then rounded once
+// if C is bf16: the merge of gemm_bf16_split, four elements per thread, up to
+// eight partial products' loads in flight.
+template <bool CBF16>
+__global__ __launch_bounds__(256) void gemm_combine_kernel(const float *W, void *C, size_t mn, int S)
+{
+    const size_t e = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;   // mn is a multiple of 16384
+    f32x4 sum = *(const f32x4 *)(W + e);
+    for (int s = 1; s < S; s += 8) {
+        f32x4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            v[u] = s + u < S ? *(const f32x4 *)(W + (s + u) * mn + e) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (s + u < S)
+                sum += v[u];
+    }
+    if (CBF16)
+        *(u32x2 *)((uint16_t *)C + e) = u32x2{pack_bf16(sum[0], sum[1]), pack_bf16(sum[2], sum[3])};
+    else
+        *(f32x4 *)((float *)C + e) = sum;
+}
+
+constexpr int GEMM_MAX_SPLITS = 64;
 
 }  // namespace
 
@@ -661,6 +697,7 @@ ta_status gemm_bf16(const void *A, const void *B, void *C, int c_bf16, int M, in
     a.M = M;
     a.N = N;
     a.K = K;
+    a.n_split = 1;
     hipStream_t s = (hipStream_t)stream;
     if (gemv) {
         const hipError_t e = run_gemv(A, B, C, c_bf16 != 0, N, K, s);
@@ -677,6 +714,111 @@ ta_status gemm_bf16(const void *A, const void *B, void *C, int c_bf16, int M, in
                          : ring ? launch<128, 128, 4, 4>(a, c_bf16 != 0, s)
                                 : launch<128, 128, 2, 2>(a, c_bf16 != 0, s);
     return e == hipSuccess ? TA_OK : TA_ERR_LAUNCH;
+}
+
+ta_status gemm_bf16_split(const void *A, const void *B, void *C, int c_bf16, int M, int N, int K,
+                          int num_splits, void *workspace, size_t workspace_bytes, void *stream)
+{
+    if (num_splits == 1)
+        return gemm_bf16(A, B, C, c_bf16, M, N, K, stream);
+    if (!A || !B || !C)
+        return TA_ERR_NULL_POINTER;
+    if (M < 1 || N < 1 || K < 1 || num_splits < 1 || num_splits > GEMM_MAX_SPLITS)
+        return TA_ERR_INVALID_SHAPE;
+    if (M % 128 || N % 128 || K % BK || num_splits > K / BK)
+        return TA_ERR_UNSUPPORTED;
+    // 32-bit offsets, as gemm_bf16; 32-bit grids
+    const int64_t mn = (int64_t)M * N;
+    if ((int64_t)K * N * 2 >= (1ll << 31) || (int64_t)M * K >= (1ll << 40) ||
+        (int64_t)256 * K * 2 >= (1ll << 31) || mn / 1024 >= (1ll << 31) ||
+        mn / (128 * 128) * num_splits >= (1ll << 31))
+        return TA_ERR_INVALID_SHAPE;
+    if (misaligned(A) || misaligned(B) || misaligned(C))
+        return TA_ERR_MISALIGNED;
+    const size_t a_bytes = (size_t)M * K * 2, b_bytes = (size_t)K * N * 2;
+    const size_t c_bytes = (size_t)mn * (c_bf16 ? 2 : 4), w_bytes = (size_t)num_splits * mn * 4;
+    if (overlaps(C, c_bytes, A, a_bytes) || overlaps(C, c_bytes, B, b_bytes))
+        return TA_ERR_ALIASING;
+    if (!workspace || workspace_bytes < w_bytes)
+        return TA_ERR_WORKSPACE;
+    if (misaligned(workspace))
+        return TA_ERR_MISALIGNED;
+    if (overlaps(workspace, w_bytes, A, a_bytes) || overlaps(workspace, w_bytes, B, b_bytes) ||
+        overlaps(workspace, w_bytes, C, c_bytes))
+        return TA_ERR_ALIASING;
+    GArgs a;
+    a.A = (const uint16_t *)A;
+    a.B = (const uint16_t *)B;
+    a.C = workspace;
+    a.M = M;
+    a.N = N;
+    a.K = K;
+    a.n_split = num_splits;
+    hipStream_t s = (hipStream_t)stream;
+    // one workgroup per CU: the four-stage ring, else two stages and two
+    // workgroups per CU (as gemm_bf16)
+    hipError_t e = mn / (128 * 128) * num_splits <= 256 ? launch<128, 128, 4, 4>(a, false, s)
+                                                        : launch<128, 128, 2, 2>(a, false, s);
+    if (e != hipSuccess)
+        return TA_ERR_LAUNCH;
+    const dim3 grid((unsigned)(mn / 1024));
+    const float *w = (const float *)workspace;
+    if (c_bf16)
+        hipLaunchKernelGGL(gemm_combine_kernel<true>, grid, dim3(256), 0, s, w, C, (size_t)mn, num_splits);
+    else
+        hipLaunchKernelGGL(gemm_combine_kernel<false>, grid, dim3(256), 0, s, w, C, (size_t)mn, num_splits);
+    e = hipGetLastError();
+    return e == hipSuccess ? TA_OK : TA_ERR_LAUNCH;
+}
+
+ta_status gemm_split_workspace_bytes(int M, int N, int num_splits, size_t *bytes)
+{
+    if (!bytes)
+        return TA_ERR_NULL_POINTER;
+    if (M < 1 || N < 1 || num_splits < 1 || num_splits > GEMM_MAX_SPLITS)
+        return TA_ERR_INVALID_SHAPE;
+    *bytes = num_splits > 1 ? (size_t)num_splits * M * N * 4 : 0;
+    return TA_OK;
+}
+
+// The split count with the smallest estimate, if that is a sixth under the
+// unsplit one (which spares the second launch and the workspace):
+//   K steps per range x us per step (0.5 with at most half of the CUs at
+//   work, 0.6 up to one workgroup per CU, 0.85 for two) + 6
+//   + for more than one range 4 + 8 M N S bytes at 4.5 TB/s.
+// Within 10 % of what was measured over 128-2048 x 384-4224 x 192-28672 (us,
+// unsplit | by S): 384 x 4224 x 8256 75 | 2: 52, 4: 48, 5: 43; 128 x 4096 x
+// 4096 38 | 2: 26, 4: 21, 8: 21; 128 x 1024 x 8192 61 | 8: 18, 16: 18, 32: 21;
+// 256 x 1024 x 28672 244 | 8: 45, 16: 33; 1024 x 1024 x 1024 14 | 2: 18; 2048 x
+// 1024 x 2048 23 | 2: 24.
+ta_status gemm_split_heuristic(int M, int N, int K, int *num_splits)
+{
+    if (!num_splits)
+        return TA_ERR_NULL_POINTER;
+    if (M < 1 || N < 1 || K < 1)
+        return TA_ERR_INVALID_SHAPE;
+    *num_splits = 1;
+    if (M % 128 || N % 128 || K % BK)
+        return TA_OK;
+    const int64_t tiles = (int64_t)(M / 128) * (N / 128);
+    const int steps = K / BK;
+    double best = 0;
+    for (int sp = 1; sp <= GEMM_MAX_SPLITS && sp <= steps && tiles * sp <= 512; ++sp) {
+        const int64_t wg = tiles * sp;
+        if (sp == 1 && wg > 256)
+            break;
+        const double per_step = wg <= 128 ? 0.5 : wg <= 256 ? 0.6 : 0.85;
+        double t = (steps + sp - 1) / sp * per_step + 6;
+        if (sp > 1)
+            t += 4 + 8.0 * M * N * sp / 4.5e6;
+        if (sp == 1)
+            best = t * (5.0 / 6.0);
+        else if (t < best) {
+            best = t;
+            *num_splits = sp;
+        }
+    }
+    return TA_OK;
 }
 
 ta_status gemv_bf16_split(const void *A, const void *B, void *C, int c_bf16, int N, int K,

@@ -64,6 +64,12 @@ def lib():
     L.mla_split_heuristic.argtypes = [i, i, i, i, ctypes.POINTER(i)]
     L.gemm_bf16.restype = i
     L.gemm_bf16.argtypes = [p, p, p, i, i, i, i, p]
+    L.gemm_bf16_split.restype = i
+    L.gemm_bf16_split.argtypes = [p, p, p, i, i, i, i, i, p, ctypes.c_size_t, p]
+    L.gemm_split_workspace_bytes.restype = i
+    L.gemm_split_workspace_bytes.argtypes = [i, i, i, ctypes.POINTER(ctypes.c_size_t)]
+    L.gemm_split_heuristic.restype = i
+    L.gemm_split_heuristic.argtypes = [i, i, i, ctypes.POINTER(i)]
     L.gemv_bf16_split.restype = i
     L.gemv_bf16_split.argtypes = [p, p, p, i, i, i, i, p, ctypes.c_size_t, p]
     L.gemv_split_workspace_bytes.restype = i
@@ -374,9 +380,35 @@ def gemm_bf16_raw(A, B, C, c_bf16, M, N, K, stream) -> int:
     return lib().gemm_bf16(A, B, C, int(bool(c_bf16)), M, N, K, stream)
 
 
-def gemm_bf16(a, b, out=None, out_dtype=None, stream=None):
+def gemm_split_workspace_bytes(M: int, N: int, num_splits: int) -> int:
+    n = ctypes.c_size_t()
+    rc = lib().gemm_split_workspace_bytes(M, N, num_splits, ctypes.byref(n))
+    if rc != TA_OK:
+        raise TileAttnError(rc, ta_status_string(rc))
+    return n.value
+
+
+def gemm_split_heuristic(M: int, N: int, K: int) -> int:
+    n = ctypes.c_int()
+    rc = lib().gemm_split_heuristic(M, N, K, ctypes.byref(n))
+    if rc != TA_OK:
+        raise TileAttnError(rc, ta_status_string(rc))
+    return n.value
+
+
+def gemm_bf16_split_raw(A, B, C, c_bf16, M, N, K, num_splits, workspace, workspace_bytes,
+                        stream) -> int:
+    """gemm_bf16_split with integer pointers; returns the status code."""
+    return lib().gemm_bf16_split(A, B, C, int(bool(c_bf16)), M, N, K, int(num_splits), workspace,
+                                 int(workspace_bytes), stream)
+
+
+def gemm_bf16(a, b, out=None, out_dtype=None, stream=None, num_splits: int | None = None):
     """C = A B for contiguous bfloat16 GPU matrices a [M, K], b [K, N]; C is
-    float32 (default) or bfloat16 (``out_dtype=torch.bfloat16``)."""
+    float32 (default) or bfloat16 (``out_dtype=torch.bfloat16``).  K is
+    summed in ``num_splits`` ranges (default gemm_split_heuristic: one unless
+    the product has few tiles and a long K), through a workspace allocated
+    here."""
     import torch
 
     for name, t in (("a", a), ("b", b)):
@@ -395,9 +427,22 @@ def gemm_bf16(a, b, out=None, out_dtype=None, stream=None):
         raise TypeError(f"out must be a contiguous {dt} tensor of shape {(M, N)}")
     if stream is None:
         stream = torch.cuda.current_stream(a.device)
+    if num_splits is None:
+        # (only products of at most 256 tiles of 128 x 128 are ever split)
+        num_splits = gemm_split_heuristic(M, N, K) if M > 1 and 1 <= M * N <= 256 << 14 and K > 0 else 1
+    ws, need = None, 0
+    if num_splits != 1:
+        need = gemm_split_workspace_bytes(M, N, num_splits)
+        ws = torch.empty(need, dtype=torch.uint8, device=a.device)
+        ws.record_stream(stream)   # as in attn_fwd_split
     with _one_device(a, b, out):
-        rc = gemm_bf16_raw(a.data_ptr(), b.data_ptr(), out.data_ptr(), dt == torch.bfloat16, M, N,
-                           K, stream.cuda_stream)
+        if ws is None:
+            rc = gemm_bf16_raw(a.data_ptr(), b.data_ptr(), out.data_ptr(), dt == torch.bfloat16,
+                               M, N, K, stream.cuda_stream)
+        else:
+            rc = gemm_bf16_split_raw(a.data_ptr(), b.data_ptr(), out.data_ptr(),
+                                     dt == torch.bfloat16, M, N, K, num_splits, ws.data_ptr(), need,
+                                     stream.cuda_stream)
     if rc != TA_OK:
         raise TileAttnError(rc, ta_status_string(rc))
     return out

@@ -305,6 +305,38 @@ def test_gemv_split_validation_before_any_hip_call(change, status):
     assert rc == status, f"{change}: got {ta.STATUS.get(rc, rc)}, want {ta.STATUS[status]}"
 
 
+@no_gpu
+def test_gemm_split_validation_before_any_hip_call():
+    ok = dict(A=GA, B=GB, C=GC, M=256, N=256, K=256, splits=3, ws=0x70000000, ws_bytes=3 * 256 * 256 * 4)
+
+    def rc(**change):
+        a = dict(ok, **change)
+        return ta.gemm_bf16_split_raw(a["A"], a["B"], a["C"], False, a["M"], a["N"], a["K"], a["splits"],
+                                      a["ws"], a["ws_bytes"], None)
+
+    for change, status in [
+            (dict(A=0), 1), (dict(C=0), 1), (dict(M=0), 2), (dict(splits=0), 2), (dict(splits=65), 2),
+            (dict(M=1), 3), (dict(M=200), 3), (dict(K=96), 3), (dict(splits=5), 3), (dict(A=GA + 8), 4),
+            (dict(ws=0x70000008), 4), (dict(C=GA), 6), (dict(ws=GB), 6), (dict(ws=GC), 6), (dict(ws=0), 8),
+            (dict(ws_bytes=3 * 256 * 256 * 4 - 1), 8), (dict(N=65536, K=16384), 2)]:
+        assert rc(**change) == status, change
+    assert rc(splits=1, A=0) == 1 and rc(splits=1, K=96) == 3   # gemm_bf16's checks
+
+
+def test_gemm_split_workspace_and_heuristic():
+    assert ta.gemm_split_workspace_bytes(384, 4224, 5) == 5 * 384 * 4224 * 4
+    assert ta.gemm_split_workspace_bytes(384, 4224, 1) == 0
+    for M, N, K in [(384, 4224, 8256), (128, 128, 28672), (128, 1024, 8192), (4096, 8192, 8192),
+                    (4096, 1024, 8192), (1024, 1024, 1024), (256, 384, 192), (1, 4096, 4096), (100, 128, 64)]:
+        n = ta.gemm_split_heuristic(M, N, K)
+        assert 1 <= n <= 64
+        tiles = (M // 128) * (N // 128)
+        assert n == 1 or (tiles * n <= 512 and n <= K // 64 and tiles <= 256)
+    # long K, few tiles: split; enough tiles or short K: not
+    assert ta.gemm_split_heuristic(384, 4224, 8256) > 1 and ta.gemm_split_heuristic(128, 1024, 8192) > 1
+    assert ta.gemm_split_heuristic(4096, 1024, 8192) == 1 and ta.gemm_split_heuristic(1024, 1024, 1024) == 1
+
+
 def test_gemv_split_workspace_and_heuristic():
     assert ta.gemv_split_workspace_bytes(9216, 7) == 7 * 9216 * 4
     assert ta.gemv_split_workspace_bytes(9216, 1) == 0

@@ -213,3 +213,31 @@ def test_gemv_split_bf16_out_and_deterministic(ta):
     assert torch.equal(c1.view(torch.int32), ref1.view(torch.int32))
     check("gemv split fp32", c32, a, b)
     check("gemv split bf16 out", c16, a, b, bf16=True)
+
+
+@pytest.mark.parametrize("shape,splits", [
+    ((128, 128, 128), 2),       # one step per range
+    ((128, 256, 192), 3),
+    ((256, 384, 1088), 5),      # 17 steps: ranges of 3 and 4
+    ((128, 128, 4096), 64),     # the most ranges
+    ((1280, 1280, 640), 3),     # more than 256 workgroups: two stages
+    ((384, 128, 8192), None),   # the heuristic's count
+], ids=str)
+def test_gemm_split_full_compare(ta, shape, splits):
+    """K ranges summed by separate workgroups and merged in order: the bound
+    of the unsplit product (fp32 sums of the same terms), bf16 C rounded once
+    from the same sums, two runs alike."""
+    M, N, K = shape
+    n = ta.gemm_split_heuristic(M, N, K) if splits is None else splits
+    print(f"gemm split {shape} {n}", flush=True)
+    assert n > 1
+    a, b = gen.random_gemm_problem(M, N, K, seed=M + N + K)
+    da, db = dev(a), dev(b)
+    c = torch.full((M, N), float("nan"), device="cuda")
+    ta.gemm_bf16(da, db, out=c, num_splits=splits)
+    c2 = ta.gemm_bf16(da, db, num_splits=n)
+    c16 = ta.gemm_bf16(da, db, out_dtype=torch.bfloat16, num_splits=splits)
+    torch.cuda.synchronize()
+    check(f"gemm split {shape}", c, a, b)
+    assert torch.equal(c, c2)
+    assert torch.equal(c16.view(torch.int16), c.to(torch.bfloat16).view(torch.int16))
