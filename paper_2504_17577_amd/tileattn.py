@@ -10,6 +10,8 @@ import ctypes
 import math
 import os
 
+import torch
+
 PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(PKG, "libtileattn.so")
 
@@ -177,22 +179,60 @@ def attn_fwd_bf16out_raw(Q, K, V, O, LSE, B, Hq, Hkv, Sq, Sk, D, causal, scale, 
                                   float(scale), stream)
 
 
+def _output(name, t, shape, dtype, like):
+    """A new output of this shape and dtype on ``like``'s device, or the given one checked."""
+    if t is None:
+        return like.new_empty(shape, dtype=dtype)
+    if t.dtype != dtype or tuple(t.shape) != shape or not t.is_contiguous():
+        raise TypeError(f"{name} must be a contiguous {dtype} tensor of shape {shape}")
+    return t
+
+
+class _Here:
+    """The context of a launch whose tensors are on the current device."""
+
+    def __enter__(self):
+        pass
+
+    def __exit__(self, *exc):
+        pass
+
+
+_HERE = _Here()
+
+
 def _one_device(*tensors):
     """A context that makes the tensors' device current for the launch (the
     library launches on the current device); raises if they are spread over
-    several devices."""
-    import torch
-
-    dev = tensors[0].device
+    several devices.  Device indices and, below, raw stream handles are read
+    without building torch's device and stream objects or switching to a
+    device that is current: small calls are bound by this host work (B=1
+    H=2 S=128 D=64: 14.2 us a call before, 9.8 now, of which the launch itself
+    takes 4.0)."""
+    dev = tensors[0].get_device()
     for t in tensors[1:]:
-        if t is not None and t.device != dev:
-            raise TypeError(f"all tensors must be on one device ({dev} and {t.device} given)")
-    return torch.cuda.device(dev)
+        if t is not None and t.get_device() != dev:
+            raise TypeError(f"all tensors must be on one device ({tensors[0].device} and {t.device} "
+                            "given)")
+    return _HERE if dev == torch._C._cuda_getDevice() else torch.cuda.device(dev)
+
+
+def _stream_handle(stream, t):
+    """The hipStream_t of ``stream`` (None: the current one of t's device)."""
+    return torch._C._cuda_getCurrentRawStream(t.get_device()) if stream is None else stream.cuda_stream
+
+
+def _workspace(need, t, stream):
+    """A workspace freed by its caller when the call returns; used on a stream
+    other than the current one, the allocator must not hand the block to other
+    work before the launch there has finished."""
+    ws = torch.empty(max(need, 16), dtype=torch.uint8, device=t.device)
+    if stream is not None:
+        ws.record_stream(stream)
+    return ws
 
 
 def _attn(q, k, v, causal, scale, out, lse, stream, o_dtype, raw):
-    import torch
-
     for name, t in (("q", q), ("k", k), ("v", v)):
         if t.dtype != torch.bfloat16 or not t.is_cuda or t.dim() != 4 or not t.is_contiguous():
             raise TypeError(f"{name} must be a contiguous 4-D bfloat16 GPU tensor (BHSD)")
@@ -203,19 +243,11 @@ def _attn(q, k, v, causal, scale, out, lse, stream, o_dtype, raw):
                                f"v{tuple(v.shape)}")
     if scale is None:
         scale = 1.0 / math.sqrt(D)
-    if out is None:
-        out = torch.empty((B, Hq, Sq, D), dtype=o_dtype, device=q.device)
-    if lse is None:
-        lse = torch.empty((B, Hq, Sq), dtype=torch.float32, device=q.device)
-    for name, t, shape, dt in (("out", out, (B, Hq, Sq, D), o_dtype),
-                               ("lse", lse, (B, Hq, Sq), torch.float32)):
-        if t.dtype != dt or tuple(t.shape) != shape or not t.is_contiguous():
-            raise TypeError(f"{name} must be a contiguous {dt} tensor of shape {shape}")
-    if stream is None:
-        stream = torch.cuda.current_stream(q.device)
+    out = _output("out", out, (B, Hq, Sq, D), o_dtype, q)
+    lse = _output("lse", lse, (B, Hq, Sq), torch.float32, q)
     with _one_device(q, k, v, out, lse):
         rc = raw(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
-                 B, Hq, Hkv, Sq, Sk, D, causal, scale, stream.cuda_stream)
+                 B, Hq, Hkv, Sq, Sk, D, causal, scale, _stream_handle(stream, q))
     if rc != TA_OK:
         raise TileAttnError(rc, ta_status_string(rc))
     return out, lse
@@ -227,8 +259,6 @@ def attn_fwd(q, k, v, causal: bool = False, scale: float | None = None, out=None
     k, v [B,Hkv,Sk,D] on the GPU.  Returns fp32 O [B,Hq,Sq,D] and
     LSE [B,Hq,Sq].  ``scale`` defaults to 1/sqrt(D).  The launch is
     asynchronous on ``stream`` (default: torch's current stream)."""
-    import torch
-
     return _attn(q, k, v, causal, scale, out, lse, stream, torch.float32, attn_fwd_raw)
 
 
@@ -236,8 +266,6 @@ def attn_fwd_bf16out(q, k, v, causal: bool = False, scale: float | None = None, 
                      lse=None, stream=None):
     """As attn_fwd, with O returned in bfloat16 (the fp32 result rounded to
     nearest even by the kernel)."""
-    import torch
-
     return _attn(q, k, v, causal, scale, out, lse, stream, torch.bfloat16, attn_fwd_bf16out_raw)
 
 
@@ -250,8 +278,6 @@ def attn_fwd_split(q, k, v, causal: bool = False, scale: float | None = None,
     ta_split_workspace_bytes(...) bytes (allocated here if None); it must
     stay alive until the launch has finished on ``stream``.  ``out_dtype``
     is torch.float32 (default) or torch.bfloat16."""
-    import torch
-
     o_dtype = torch.float32 if out_dtype is None else out_dtype
     if o_dtype not in (torch.float32, torch.bfloat16):
         raise TypeError("out_dtype must be torch.float32 or torch.bfloat16")
@@ -261,13 +287,8 @@ def attn_fwd_split(q, k, v, causal: bool = False, scale: float | None = None,
         plan = ta_split_plan if workspace is None else ta_split_heuristic
         num_splits = plan(B, Hq, Hkv, Sq, Sk, D, causal)
     need = ta_split_workspace_bytes(B, Hq, Sq, D, num_splits)
-    if stream is None:
-        stream = torch.cuda.current_stream(q.device)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
-        # freed when this call returns: keep the allocator from handing the
-        # block to other work before the launch on ``stream`` has finished
-        workspace.record_stream(stream)
+        workspace = _workspace(need, q, stream)
     if (workspace.dtype != torch.uint8 or workspace.device != q.device
             or not workspace.is_contiguous()):
         raise TypeError("workspace must be a contiguous uint8 tensor on q's device")
@@ -287,8 +308,6 @@ def attn_fwd_split_noalloc(q, k, v, causal: bool = False, scale: float | None = 
     per-GPU scratch instead of a workspace (the C call allocates nothing;
     pass ``out`` and ``lse`` to allocate nothing here either).  Calls that
     overlap on one GPU race on that scratch."""
-    import torch
-
     o_dtype = torch.float32 if out_dtype is None else out_dtype
     if o_dtype not in (torch.float32, torch.bfloat16):
         raise TypeError("out_dtype must be torch.float32 or torch.bfloat16")
@@ -334,8 +353,6 @@ def mla_decode(q, q_pe, kv, k_pe, scale: float | None = None, num_splits: int | 
     mla_split_heuristic.  ``workspace`` (uint8 GPU tensor) is allocated here
     if needed and not given; it must stay alive until the launch has
     finished on ``stream``."""
-    import torch
-
     for name, t, nd in (("q", q, 3), ("q_pe", q_pe, 3), ("kv", kv, 4), ("k_pe", k_pe, 4)):
         if t.dtype != torch.bfloat16 or not t.is_cuda or t.dim() != nd or not t.is_contiguous():
             raise TypeError(f"{name} must be a contiguous {nd}-D bfloat16 GPU tensor")
@@ -350,26 +367,18 @@ def mla_decode(q, q_pe, kv, k_pe, scale: float | None = None, num_splits: int | 
         scale = 1.0 / math.sqrt(Dl + Dr)
     if num_splits is None:
         num_splits = mla_split_heuristic(B, H, Hkv, Skv)
-    if out is None:
-        out = torch.empty((B, H, Dl), dtype=torch.float32, device=q.device)
-    if lse is None:
-        lse = torch.empty((B, H), dtype=torch.float32, device=q.device)
-    for name, t, shape in (("out", out, (B, H, Dl)), ("lse", lse, (B, H))):
-        if t.dtype != torch.float32 or tuple(t.shape) != shape or not t.is_contiguous():
-            raise TypeError(f"{name} must be a contiguous float32 tensor of shape {shape}")
+    out = _output("out", out, (B, H, Dl), torch.float32, q)
+    lse = _output("lse", lse, (B, H), torch.float32, q)
     need = mla_workspace_bytes(B, H, num_splits)
-    if stream is None:
-        stream = torch.cuda.current_stream(q.device)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
-        workspace.record_stream(stream)   # as in attn_fwd_split
+        workspace = _workspace(need, q, stream)
     if workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
         raise TypeError("workspace must be a contiguous uint8 GPU tensor")
     with _one_device(q, q_pe, kv, k_pe, out, lse, workspace):
         rc = mla_decode_raw(q.data_ptr(), q_pe.data_ptr(), kv.data_ptr(), k_pe.data_ptr(),
                             out.data_ptr(), lse.data_ptr(), B, H, Hkv, Skv, Dl, Dr, scale,
                             num_splits, workspace.data_ptr(), workspace.numel(),
-                            stream.cuda_stream)
+                            _stream_handle(stream, q))
     if rc != TA_OK:
         raise TileAttnError(rc, ta_status_string(rc))
     return out, lse
@@ -409,8 +418,6 @@ def gemm_bf16(a, b, out=None, out_dtype=None, stream=None, num_splits: int | Non
     summed in ``num_splits`` ranges (default gemm_split_heuristic: one unless
     the product has few tiles and a long K), through a workspace allocated
     here."""
-    import torch
-
     for name, t in (("a", a), ("b", b)):
         if t.dtype != torch.bfloat16 or not t.is_cuda or t.dim() != 2 or not t.is_contiguous():
             raise TypeError(f"{name} must be a contiguous 2-D bfloat16 GPU tensor")
@@ -421,28 +428,22 @@ def gemm_bf16(a, b, out=None, out_dtype=None, stream=None, num_splits: int | Non
     dt = torch.float32 if out_dtype is None else out_dtype
     if dt not in (torch.float32, torch.bfloat16):
         raise TypeError("out_dtype must be torch.float32 or torch.bfloat16")
-    if out is None:
-        out = torch.empty((M, N), dtype=dt, device=a.device)
-    if out.dtype != dt or tuple(out.shape) != (M, N) or not out.is_contiguous():
-        raise TypeError(f"out must be a contiguous {dt} tensor of shape {(M, N)}")
-    if stream is None:
-        stream = torch.cuda.current_stream(a.device)
+    out = _output("out", out, (M, N), dt, a)
     if num_splits is None:
         # (only products of at most 256 tiles of 128 x 128 are ever split)
         num_splits = gemm_split_heuristic(M, N, K) if M > 1 and 1 <= M * N <= 256 << 14 and K > 0 else 1
     ws, need = None, 0
     if num_splits != 1:
         need = gemm_split_workspace_bytes(M, N, num_splits)
-        ws = torch.empty(need, dtype=torch.uint8, device=a.device)
-        ws.record_stream(stream)   # as in attn_fwd_split
+        ws = _workspace(need, a, stream)
     with _one_device(a, b, out):
         if ws is None:
             rc = gemm_bf16_raw(a.data_ptr(), b.data_ptr(), out.data_ptr(), dt == torch.bfloat16,
-                               M, N, K, stream.cuda_stream)
+                               M, N, K, _stream_handle(stream, a))
         else:
             rc = gemm_bf16_split_raw(a.data_ptr(), b.data_ptr(), out.data_ptr(),
                                      dt == torch.bfloat16, M, N, K, num_splits, ws.data_ptr(), need,
-                                     stream.cuda_stream)
+                                     _stream_handle(stream, a))
     if rc != TA_OK:
         raise TileAttnError(rc, ta_status_string(rc))
     return out
@@ -478,8 +479,6 @@ def gemv_bf16_split(a, b, num_splits: int | None = None, out=None, out_dtype=Non
     float32 (default) or bfloat16.  ``workspace`` (uint8 GPU tensor) is
     allocated here if needed and not given; it must stay alive until the
     launch has finished on ``stream``."""
-    import torch
-
     for name, t in (("a", a), ("b", b)):
         if t.dtype != torch.bfloat16 or not t.is_cuda or t.dim() != 2 or not t.is_contiguous():
             raise TypeError(f"{name} must be a contiguous 2-D bfloat16 GPU tensor")
@@ -492,22 +491,16 @@ def gemv_bf16_split(a, b, num_splits: int | None = None, out=None, out_dtype=Non
         raise TypeError("out_dtype must be torch.float32 or torch.bfloat16")
     if num_splits is None:
         num_splits = gemv_split_heuristic(N, K)
-    if out is None:
-        out = torch.empty((1, N), dtype=dt, device=a.device)
-    if out.dtype != dt or tuple(out.shape) != (1, N) or not out.is_contiguous():
-        raise TypeError(f"out must be a contiguous {dt} tensor of shape {(1, N)}")
+    out = _output("out", out, (1, N), dt, a)
     need = gemv_split_workspace_bytes(N, num_splits)
-    if stream is None:
-        stream = torch.cuda.current_stream(a.device)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=a.device)
-        workspace.record_stream(stream)   # as in attn_fwd_split
+        workspace = _workspace(need, a, stream)
     if workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
         raise TypeError("workspace must be a contiguous uint8 GPU tensor")
     with _one_device(a, b, out, workspace):
         rc = gemv_bf16_split_raw(a.data_ptr(), b.data_ptr(), out.data_ptr(), dt == torch.bfloat16,
                                  N, K, num_splits, workspace.data_ptr(), workspace.numel(),
-                                 stream.cuda_stream)
+                                 _stream_handle(stream, a))
     if rc != TA_OK:
         raise TileAttnError(rc, ta_status_string(rc))
     return out
@@ -522,8 +515,6 @@ SSD_CHUNK = 256
 
 
 def _ssd_check(name, t, dtype, shape):
-    import torch
-
     if t.dtype != dtype or not t.is_cuda or tuple(t.shape) != tuple(shape) or not t.is_contiguous():
         raise TypeError(f"{name} must be a contiguous {dtype} GPU tensor of shape {tuple(shape)}")
 
@@ -541,8 +532,6 @@ def _ssd_raise(rc):
 
 def ssd_chunk_state(x, Bm, dt, A, out=None, stream=None):
     """states [B, nc, H, P, N] fp32 of each chunk started from zero."""
-    import torch
-
     Bsz, L, H, G, P, N, nc = _ssd_dims(x, Bm)
     _ssd_check("x", x, torch.bfloat16, (Bsz, L, H, P))
     _ssd_check("Bm", Bm, torch.bfloat16, (Bsz, L, G, N))
@@ -551,19 +540,16 @@ def ssd_chunk_state(x, Bm, dt, A, out=None, stream=None):
     if out is None:
         out = torch.empty((Bsz, nc, H, P, N), dtype=torch.float32, device=x.device)
     _ssd_check("out", out, torch.float32, (Bsz, nc, H, P, N))
-    stream = stream or torch.cuda.current_stream(x.device)
     with _one_device(x, Bm, dt, A, out):
         _ssd_raise(lib().ssd_chunk_state(x.data_ptr(), Bm.data_ptr(), dt.data_ptr(), A.data_ptr(),
                                          out.data_ptr(), Bsz, L, H, G, P, N, SSD_CHUNK,
-                                         stream.cuda_stream))
+                                         _stream_handle(stream, x)))
     return out
 
 
 def ssd_state_passing(states, dt, A, prev=None, final=None, stream=None):
     """(prev_states [B, nc, H, P, N], final_states [B, H, P, N]): the state
     each chunk enters with, and the state after the last chunk."""
-    import torch
-
     Bsz, nc, H, P, N = states.shape
     L = dt.shape[1]
     _ssd_check("states", states, torch.float32, (Bsz, nc, H, P, N))
@@ -577,18 +563,15 @@ def ssd_state_passing(states, dt, A, prev=None, final=None, stream=None):
         final = torch.empty((Bsz, H, P, N), dtype=torch.float32, device=states.device)
     _ssd_check("prev", prev, torch.float32, (Bsz, nc, H, P, N))
     _ssd_check("final", final, torch.float32, (Bsz, H, P, N))
-    stream = stream or torch.cuda.current_stream(states.device)
     with _one_device(states, dt, A, prev, final):
         _ssd_raise(lib().ssd_state_passing(states.data_ptr(), dt.data_ptr(), A.data_ptr(),
                                            prev.data_ptr(), final.data_ptr(), Bsz, L, H, P, N,
-                                           SSD_CHUNK, stream.cuda_stream))
+                                           SSD_CHUNK, _stream_handle(stream, states)))
     return prev, final
 
 
 def ssd_bmm_chunk(Cm, Bm, out=None, stream=None):
     """cb [B, nc, G, Q, Q] fp32: cb[l][s] = Cm_l . Bm_s inside each chunk."""
-    import torch
-
     Bsz, L, G, N = Cm.shape
     nc = -(-L // SSD_CHUNK)
     _ssd_check("Cm", Cm, torch.bfloat16, (Bsz, L, G, N))
@@ -596,17 +579,14 @@ def ssd_bmm_chunk(Cm, Bm, out=None, stream=None):
     if out is None:
         out = torch.empty((Bsz, nc, G, SSD_CHUNK, SSD_CHUNK), dtype=torch.float32, device=Cm.device)
     _ssd_check("out", out, torch.float32, (Bsz, nc, G, SSD_CHUNK, SSD_CHUNK))
-    stream = stream or torch.cuda.current_stream(Cm.device)
     with _one_device(Cm, Bm, out):
         _ssd_raise(lib().ssd_bmm_chunk(Cm.data_ptr(), Bm.data_ptr(), out.data_ptr(), Bsz, L, G, N,
-                                       SSD_CHUNK, stream.cuda_stream))
+                                       SSD_CHUNK, _stream_handle(stream, Cm)))
     return out
 
 
 def ssd_chunk_scan(x, Cm, cb, dt, A, prev_states, D=None, out=None, stream=None):
     """y [B, L, H, P] fp32 of the chunk-scan function."""
-    import torch
-
     Bsz, L, H, G, P, N, nc = _ssd_dims(x, Cm)
     _ssd_check("x", x, torch.bfloat16, (Bsz, L, H, P))
     _ssd_check("Cm", Cm, torch.bfloat16, (Bsz, L, G, N))
@@ -619,12 +599,11 @@ def ssd_chunk_scan(x, Cm, cb, dt, A, prev_states, D=None, out=None, stream=None)
     if out is None:
         out = torch.empty((Bsz, L, H, P), dtype=torch.float32, device=x.device)
     _ssd_check("out", out, torch.float32, (Bsz, L, H, P))
-    stream = stream or torch.cuda.current_stream(x.device)
     with _one_device(x, Cm, cb, dt, A, prev_states, D, out):
         _ssd_raise(lib().ssd_chunk_scan(x.data_ptr(), Cm.data_ptr(), cb.data_ptr(), dt.data_ptr(),
                                         A.data_ptr(), prev_states.data_ptr(),
                                         D.data_ptr() if D is not None else None, out.data_ptr(),
-                                        Bsz, L, H, G, P, N, SSD_CHUNK, stream.cuda_stream))
+                                        Bsz, L, H, G, P, N, SSD_CHUNK, _stream_handle(stream, x)))
     return out
 
 
@@ -646,8 +625,6 @@ def ssd_forward(x, dt, A, Bm, Cm, D=None, stream=None, num_segments: int | None 
     what the four SSD functions give chained, in one call.  ``num_segments``
     (default ssd_segment_heuristic) is the number of pieces of the sequence
     that run in parallel."""
-    import torch
-
     Bsz, L, H, G, P, N, _ = _ssd_dims(x, Bm)
     _ssd_check("x", x, torch.bfloat16, (Bsz, L, H, P))
     _ssd_check("Bm", Bm, torch.bfloat16, (Bsz, L, G, N))
@@ -661,7 +638,6 @@ def ssd_forward(x, dt, A, Bm, Cm, D=None, stream=None, num_segments: int | None 
         prev, final = ssd_state_passing(states, dt, A, stream=stream)
         cb = ssd_bmm_chunk(Cm, Bm, stream=stream)
         return ssd_chunk_scan(x, Cm, cb, dt, A, prev, D, stream=stream), final
-    stream = stream or torch.cuda.current_stream(x.device)
     if num_segments is None:
         num_segments = ssd_segment_heuristic(Bsz, L, H)
     need = ssd_forward_workspace_bytes(Bsz, L, H, num_segments)
@@ -669,12 +645,11 @@ def ssd_forward(x, dt, A, Bm, Cm, D=None, stream=None, num_segments: int | None 
     final = torch.empty((Bsz, H, P, N), dtype=torch.float32, device=x.device)
     ws = None
     if need:
-        ws = torch.empty(need, dtype=torch.uint8, device=x.device)
-        ws.record_stream(stream)   # as in attn_fwd_split
+        ws = _workspace(need, x, stream)
     with _one_device(x, Bm, Cm, dt, A, D, out):
         _ssd_raise(lib().ssd_forward(x.data_ptr(), Bm.data_ptr(), Cm.data_ptr(), dt.data_ptr(),
                                      A.data_ptr(), D.data_ptr() if D is not None else None,
                                      out.data_ptr(), final.data_ptr(), Bsz, L, H, G, P, N,
                                      num_segments, ws.data_ptr() if need else None, need,
-                                     stream.cuda_stream))
+                                     _stream_handle(stream, x)))
     return out, final
