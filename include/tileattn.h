@@ -207,10 +207,15 @@ ta_status mla_decode(const void *Q, const void *Q_pe, const void *KV, const void
 ta_status mla_workspace_bytes(int B, int H, int num_splits, size_t *bytes);
 
 /* A split count for mla_decode: enough splits of the cache for one
- * workgroup per CU (a workgroup covers 128 query heads of one latent head and
- * fills its CU's registers), keeping at least 8 tiles (256 positions) per
+ * workgroup per CU (a workgroup covers up to 128 query heads of one latent
+ * head and fills its CU's registers), keeping at least 8 tiles (256 positions) per
  * split.  No HIP call. */
 ta_status mla_split_heuristic(int B, int H, int Hkv, int Skv, int *num_splits);
+
+/* A split count for mla_decode callers that size the workspace after it: the
+ * one with the smallest time by an estimate that counts the rounds of one
+ * workgroup per CU, their tiles and the merge.  No HIP call. */
+ta_status mla_split_plan(int B, int H, int Hkv, int Skv, int *num_splits);
 
 /*
  * gemm_bf16 — C = A B: the kernel beneath the paper's Matmul listing

@@ -544,6 +544,15 @@ void mla_split_shape(int Skv, int num_splits, int *split_tiles, int *n_split)
     *n_split = (n_tiles + per - 1) / per;
 }
 
+// query heads per workgroup for `n` (batch, latent head, split) triples
+int heads_per_wg(int64_t n, int g)
+{
+    int hb = HB;
+    while (hb > HW && n * ((g + hb / 2 - 1) / (hb / 2)) <= MLA_TARGET_WG)
+        hb /= 2;
+    return hb;
+}
+
 size_t mla_ws_bytes(int B, int H, int num_splits)
 {
     return (size_t)num_splits * B * H * (size_t)(DL + 1) * 4;
@@ -641,9 +650,7 @@ ta_status mla_decode(const void *Q, const void *Q_pe, const void *KV, const void
     // from their XCD's L2.  (us, 128 heads per workgroup -> this: B=1 H=128
     // Skv=1 15 -> 8; B=4 Skv=1999 39 -> 26; B=1 Skv=8192 41 -> 29; B=16
     // Skv=1999 46 -> 34; going on to two workgroups per CU: 34 -> 49.)
-    a.hb = HB;
-    while (a.hb > HW && (int64_t)B * Hkv * ((g + a.hb / 2 - 1) / (a.hb / 2)) * n_split <= MLA_TARGET_WG)
-        a.hb /= 2;
+    a.hb = heads_per_wg((int64_t)B * Hkv * n_split, g);
     a.n_hblk = (g + a.hb - 1) / a.hb;
     a.n_wg = B * Hkv * a.n_hblk * n_split;
     if (a.n_hblk == 1)
@@ -683,6 +690,46 @@ ta_status mla_split_heuristic(int B, int H, int Hkv, int Skv, int *num_splits)
         n = n > 1 ? n : 1;
     }
     *num_splits = n;
+    return TA_OK;
+}
+
+// The split count with the smallest estimate (a larger one has to be 5 %
+// better): rounds of one workgroup per CU, each its tiles at 1.1, 1.35, 1.55 or
+// 2.45 us and 7.5, 8, 9 or 11 us besides for 16, 32, 64 or 128 heads, and for
+// more than one split a merge of 2.5 us, 1.2 for every eight splits and the
+// partial results once and a half at 5 TB/s.  Measured (us by count; * the
+// heuristic's): B=64 Skv=8192 2: 208, 4*: 191; B=48 Skv=5000 2: 116, 5: 103, 6*:
+// 153; B=100 Skv=1000 1: 56, 2: 66, 3*: 93; B=32 Skv=4096 4: 67, 8*: 69; B=16
+// Skv=500 1: 27, 2*: 26, 4: 27; B=8 Skv=500 2*: 22, 4: 20, 8: 22; B=4 Skv=1999
+// 7*: 26, 8: 25, 16: 26; B=1 Skv=500 2*: 20, 4: 15, 8: 14; B=3 H=64 Hkv=2
+// Skv=5648 22*: 25, 36: 29.
+ta_status mla_split_plan(int B, int H, int Hkv, int Skv, int *num_splits)
+{
+    if (!num_splits)
+        return TA_ERR_NULL_POINTER;
+    if (B < 1 || H < 1 || Hkv < 1 || Skv < 1 || H % Hkv != 0)
+        return TA_ERR_INVALID_SHAPE;
+    const int64_t n = (int64_t)B * Hkv;
+    const int g = H / Hkv, n_tiles = (Skv + BN - 1) / BN;
+    double best = 0;
+    *num_splits = 1;
+    for (int sp = 1; sp <= MAX_SPLITS && sp <= n_tiles; ++sp) {
+        if (sp > 1 && n * ((g + HB - 1) / HB) * sp > MLA_TARGET_WG)
+            break;
+        const int hb = heads_per_wg(n * sp, g);
+        const int busy = g < hb ? g : hb;   // heads at work
+        const int64_t wg = n * sp * ((g + hb - 1) / hb);
+        const double tile = busy <= 16 ? 1.1 : busy <= 32 ? 1.35 : busy <= 64 ? 1.55 : 2.45;
+        const double base = busy <= 16 ? 7.5 : busy <= 32 ? 8 : busy <= 64 ? 9 : 11;
+        double t = (double)((wg + MLA_TARGET_WG - 1) / MLA_TARGET_WG) *
+                   ((n_tiles + sp - 1) / sp * tile + base);
+        if (sp > 1)
+            t += 2.5 + 1.2 * ((sp + 7) / 8) + 1.5 * (double)mla_ws_bytes(B, H, sp) / 5e6;
+        if (sp == 1 || t < 0.95 * best) {
+            best = t;
+            *num_splits = sp;
+        }
+    }
     return TA_OK;
 }
 

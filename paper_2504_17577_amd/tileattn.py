@@ -64,6 +64,8 @@ def lib():
     L.mla_workspace_bytes.argtypes = [i, i, i, ctypes.POINTER(ctypes.c_size_t)]
     L.mla_split_heuristic.restype = i
     L.mla_split_heuristic.argtypes = [i, i, i, i, ctypes.POINTER(i)]
+    L.mla_split_plan.restype = i
+    L.mla_split_plan.argtypes = [i, i, i, i, ctypes.POINTER(i)]
     L.gemm_bf16.restype = i
     L.gemm_bf16.argtypes = [p, p, p, i, i, i, i, p]
     L.gemm_bf16_split.restype = i
@@ -338,6 +340,14 @@ def mla_split_heuristic(B: int, H: int, Hkv: int, Skv: int) -> int:
     return n.value
 
 
+def mla_split_plan(B: int, H: int, Hkv: int, Skv: int) -> int:
+    n = ctypes.c_int()
+    rc = lib().mla_split_plan(B, H, Hkv, Skv, ctypes.byref(n))
+    if rc != TA_OK:
+        raise TileAttnError(rc, ta_status_string(rc))
+    return n.value
+
+
 def mla_decode_raw(Q, Q_pe, KV, K_pe, O, LSE, B, H, Hkv, Skv, Dl, Dr, scale, num_splits,
                    workspace, workspace_bytes, stream) -> int:
     """mla_decode with integer pointers; returns the status code."""
@@ -350,7 +360,7 @@ def mla_decode(q, q_pe, kv, k_pe, scale: float | None = None, num_splits: int | 
     """O [B,H,Dl] fp32, LSE [B,H] fp32 = one MLA decode step of bf16 GPU
     tensors q [B,H,Dl], q_pe [B,H,Dr], kv [B,Skv,Hkv,Dl], k_pe [B,Skv,Hkv,Dr].
     ``scale`` defaults to 1/sqrt(Dl + Dr); ``num_splits`` to
-    mla_split_heuristic.  ``workspace`` (uint8 GPU tensor) is allocated here
+    mla_split_heuristic with a given workspace, else mla_split_plan.  ``workspace`` (uint8 GPU tensor) is allocated here
     if needed and not given; it must stay alive until the launch has
     finished on ``stream``."""
     for name, t, nd in (("q", q, 3), ("q_pe", q_pe, 3), ("kv", kv, 4), ("k_pe", k_pe, 4)):
@@ -366,7 +376,8 @@ def mla_decode(q, q_pe, kv, k_pe, scale: float | None = None, num_splits: int | 
     if scale is None:
         scale = 1.0 / math.sqrt(Dl + Dr)
     if num_splits is None:
-        num_splits = mla_split_heuristic(B, H, Hkv, Skv)
+        plan = mla_split_plan if workspace is None else mla_split_heuristic
+        num_splits = plan(B, H, Hkv, Skv)
     out = _output("out", out, (B, H, Dl), torch.float32, q)
     lse = _output("lse", lse, (B, H), torch.float32, q)
     need = mla_workspace_bytes(B, H, num_splits)

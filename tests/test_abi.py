@@ -256,6 +256,20 @@ def test_mla_workspace_and_heuristic():
             assert tiles // 8 <= 1
 
 
+def test_mla_split_plan():
+    for B, H, Hkv, Skv in [(64, 128, 1, 8192), (100, 128, 1, 1000), (1, 128, 1, 64), (2, 16, 1, 200),
+                           (8, 64, 2, 2048), (512, 128, 1, 4096), (1, 256, 1, 1 << 20), (3, 7, 7, 1)]:
+        n = ta.mla_split_plan(B, H, Hkv, Skv)
+        wg = B * Hkv * -(-(H // Hkv) // 128)
+        assert 1 <= n <= 128 and n <= -(-Skv // 32)
+        assert n == 1 or n * wg <= 256            # never a second round for the sake of a split
+    # counts that were measured best, or within a few per cent of it
+    assert ta.mla_split_plan(64, 128, 1, 8192) == 4 and ta.mla_split_plan(48, 128, 1, 5000) == 5
+    assert ta.mla_split_plan(100, 128, 1, 1000) == 1 and ta.mla_split_plan(16, 128, 1, 8192) == 8
+    with pytest.raises(ta.TileAttnError):
+        ta.mla_split_plan(1, 128, 3, 64)
+
+
 # gemm_bf16: argument errors before any HIP call (fake pointers)
 GA, GB, GC = 0x10000000, 0x30000000, 0x50000000
 GEMM_OK = dict(A=GA, B=GB, C=GC, c_bf16=0, M=256, N=256, K=128, stream=None)
