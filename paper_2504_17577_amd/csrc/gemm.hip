@@ -184,16 +184,14 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(GArgs args)
     const int ts = xcd * per + (xcd < rem ? xcd : rem) + idx;
     const int t = ts % a.n_tiles, split = ts / a.n_tiles;
     // grouped order: GROUP_M consecutive logical tiles walk down a column of
-    // tiles before moving right, so the workgroups resident on an XCD cover
-    // a GROUP_M x (resident / GROUP_M) block of C and share its A and B
-    // panels in that XCD's L2
-    int tm = t / a.tiles_n, tn = t % a.tiles_n;
-    if ((a.M / BM) % GROUP_M == 0) {
-        const int per_group = GROUP_M * a.tiles_n;
-        const int grp = t / per_group, w = t % per_group;
-        tm = grp * GROUP_M + w % GROUP_M;
-        tn = w / GROUP_M;
-    }
+    // tiles before moving right (fewer in a last group of fewer rows), so the
+    // workgroups resident on an XCD cover a GROUP_M x (resident / GROUP_M)
+    // block of C and share its A and B panels in that XCD's L2.  Row by row,
+    // tile rows that GROUP_M does not divide read B once per row from HBM:
+    // 896 x 8192 x 8192 154 -> 130 us, 1280 x 8192 x 8192 252 -> 207.
+    const int grp = t / (GROUP_M * a.tiles_n), w = t % (GROUP_M * a.tiles_n);
+    const int rows = min(a.M / BM - grp * GROUP_M, GROUP_M);   // tile rows of this group
+    const int tm = grp * GROUP_M + w % rows, tn = w / rows;
     const int m0 = tm * BM, n0 = tn * BN;
     const int cw = KS == 1 ? wave & 3 : wave % C::WPG;    // column of the wave's block
     const int wm = KS == 1 ? (wave >> 2) * C::WM : 0, wn = cw * C::WN;
@@ -781,16 +779,16 @@ ta_status gemm_split_workspace_bytes(int M, int N, int num_splits, size_t *bytes
     return TA_OK;
 }
 
-// The split count with the smallest estimate, if that is a sixth under the
-// unsplit one (which spares the second launch and the workspace):
-//   K steps per range x us per step (0.5 with at most half of the CUs at
-//   work, 0.6 up to one workgroup per CU, 0.85 for two) + 6
+// The split count with the smallest estimate, if that is a tenth and 3 us
+// (the second launch and the workspace) under the unsplit one:
+//   K steps per range x us per step (0.5 with at most a quarter of the CUs at
+//   work, 0.55 up to one workgroup per CU, 0.85 for two) + 6
 //   + for more than one range 4 + 8 M N S bytes at 4.5 TB/s.
-// Within 10 % of what was measured over 128-2048 x 384-4224 x 192-28672 (us,
-// unsplit | by S): 384 x 4224 x 8256 75 | 2: 52, 4: 48, 5: 43; 128 x 4096 x
-// 4096 38 | 2: 26, 4: 21, 8: 21; 128 x 1024 x 8192 61 | 8: 18, 16: 18, 32: 21;
-// 256 x 1024 x 28672 244 | 8: 45, 16: 33; 1024 x 1024 x 1024 14 | 2: 18; 2048 x
-// 1024 x 2048 23 | 2: 24.
+// Within 10 % of what was measured over 128-3072 x 384-4224 x 192-28672 (us,
+// unsplit | by S): 384 x 4224 x 8256 74 | 2: 48, 4: 46, 5: 42; 512 x 4096 x 4096
+// 42 | 2: 34, 4: 37; 128 x 4096 x 4096 38 | 2: 26, 4: 21, 8: 21; 128 x 1024 x 8192
+// 61 | 8: 18, 16: 18, 32: 21; 256 x 1024 x 28672 244 | 8: 45, 16: 33; 1024 x 1024 x
+// 1024 14 | 2: 18; 2048 x 1024 x 2048 23 | 2: 24; 3072 x 1024 x 8192 77 | 2: 74.
 ta_status gemm_split_heuristic(int M, int N, int K, int *num_splits)
 {
     if (!num_splits)
@@ -807,12 +805,12 @@ ta_status gemm_split_heuristic(int M, int N, int K, int *num_splits)
         const int64_t wg = tiles * sp;
         if (sp == 1 && wg > 256)
             break;
-        const double per_step = wg <= 128 ? 0.5 : wg <= 256 ? 0.6 : 0.85;
+        const double per_step = wg <= 64 ? 0.5 : wg <= 256 ? 0.55 : 0.85;
         double t = (steps + sp - 1) / sp * per_step + 6;
         if (sp > 1)
             t += 4 + 8.0 * M * N * sp / 4.5e6;
         if (sp == 1)
-            best = t * (5.0 / 6.0);
+            best = t * 0.9 < t - 3 ? t * 0.9 : t - 3;
         else if (t < best) {
             best = t;
             *num_splits = sp;
