@@ -783,8 +783,11 @@ __device__ __forceinline__ void buf_store(brsrc_t r, uint32_t off, f32x4 v)
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, off, 0, NT ? AUX_NT : 0);
 }
 
+// (Two workgroups per CU for one head as well: 50 KB of LDS would allow three,
+// but 168 registers spill; B=4 H=64 L=2048 88 -> 84 us, B=64 H=24 in groups of
+// three heads 483 -> 475.)
 template <int NH, bool STATE_ONLY, bool STREAM>
-__global__ __launch_bounds__(NT, NH == 1 ? 3 : 2) void ssd_forward_kernel(FwdArgs args)
+__global__ __launch_bounds__(NT, 2) void ssd_forward_kernel(FwdArgs args)
 {
     const FwdArgs &a = args;
     constexpr int PB = NH, WPH = 4 / NH;     // waves per head, 16 PB head dims each
