@@ -182,7 +182,8 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(GArgs args)
     const int per = a.n_wg / NXCD, rem = a.n_wg % NXCD;
     const int xcd = blockIdx.x % NXCD, idx = blockIdx.x / NXCD;
     const int ts = xcd * per + (xcd < rem ? xcd : rem) + idx;
-    const int t = ts % a.n_tiles, split = ts / a.n_tiles;
+    const uint32_t split = a.n_split > 1 ? ts / a.n_tiles : 0;
+    const int t = ts - split * a.n_tiles;
     // grouped order: GROUP_M consecutive logical tiles walk down a column of
     // tiles before moving right (fewer in a last group of fewer rows), so the
     // workgroups resident on an XCD cover a GROUP_M x (resident / GROUP_M)
@@ -215,10 +216,14 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(GArgs args)
         b_off[i] = (uint32_t)r * a.N * 2 + 16 * (sc ^ b_swz<MF>(r));
     }
 
-    // this range's K steps (ranges of whole steps, as even as they go)
-    const int kt_all = a.K / BK;
-    const int kt_lo = (int)((int64_t)kt_all * split / a.n_split);
-    const int n_kt = (int)((int64_t)kt_all * (split + 1) / a.n_split) - kt_lo;
+    // this range's K steps (ranges of whole steps, as even as they go; K * N <
+    // 2^30 and N >= 128, so the products fit 32 bits)
+    const uint32_t kt_all = a.K / BK;
+    int kt_lo = 0, n_kt = kt_all;
+    if (a.n_split > 1) {
+        kt_lo = kt_all * split / a.n_split;
+        n_kt = kt_all * (split + 1) / a.n_split - kt_lo;
+    }
 
     auto dma = [&](int kt, unsigned char *as, unsigned char *bs) {
         const int k0 = (kt_lo + kt) * BK;
