@@ -668,9 +668,9 @@ __global__ __launch_bounds__(NT, 4) void state_passing_kernel(PassArgs args)
 // 3.5.  Here a workgroup of four waves walks the sequence of one or two heads
 // (NH) of a group in steps of FQ = 64 positions with the state in registers
 // (fp32), so x is read and y written once and nothing else moves: 2.06 ms ->
-// 0.96 ms there.  The same traffic without the arithmetic takes 0.58 ms, the
+// 0.92 ms there.  The same traffic without the arithmetic takes 0.58 ms, the
 // arithmetic without the stores 0.75: what bounds it is the instructions of
-// the two waves that share a SIMD (VALU issue 48 %, matrix cores 25 % of the
+// the two waves that share a SIMD (VALU issue 41 %, matrix cores 27 % of the
 // time) and their waits on each other.
 //  * A head's state S^T[n][p] and y^T[p][l] are split over 4 / NH waves, 16 NH
 //    head dims each (16 x 16 accumulator blocks, lane = dim p of the state,
@@ -689,7 +689,11 @@ __global__ __launch_bounds__(NT, 4) void state_passing_kernel(PassArgs args)
 //    is dead at the barrier behind it, so that a step has two barriers.
 //  * The next step's tiles are loaded into registers during the current one,
 //    and y leaves by range-checked buffer stores: a branch around them would
-//    make the wait for the tiles one for the stores as well.
+//    make the wait for the tiles one for the stores as well.  A store covers
+//    64 bytes of each of 16 rows, two of them a line, so y is stored with the
+//    ordinary policy even where x is read with the non-temporal one: L2 then
+//    puts the lines together (non-temporal, 3.01 GB written for 2.28, 947 ->
+//    907 us).
 // STATE_ONLY: the same walk without C and y, for the state of a segment
 // started from zero (see ssd_forward).
 
@@ -777,10 +781,9 @@ __device__ __forceinline__ u32x4 buf_load(brsrc_t r, uint32_t off)
 {
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, NT ? AUX_NT : 0));
 }
-template <bool NT>
 __device__ __forceinline__ void buf_store(brsrc_t r, uint32_t off, f32x4 v)
 {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, off, 0, NT ? AUX_NT : 0);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, off, 0, 0);
 }
 
 // (Two workgroups per CU for one head as well: 50 KB of LDS would allow three,
@@ -1106,7 +1109,7 @@ __global__ __launch_bounds__(NT, 2) void ssd_forward_kernel(FwdArgs args)
                 }
 #pragma unroll
                 for (int pb = 0; pb < PB; ++pb)
-                    buf_store<STREAM>(ry, ygo + lb * 16 * ypitch + pb * 64, y[pb][lb]);
+                    buf_store(ry, ygo + lb * 16 * ypitch + pb * 64, y[pb][lb]);
             }
         }
         if (t0 + FQ >= t_hi)
