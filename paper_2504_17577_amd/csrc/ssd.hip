@@ -667,8 +667,8 @@ __global__ __launch_bounds__(NT, 4) void state_passing_kernel(PassArgs args)
 // times and x twice, 9.7 GB at B=64 L=2048 H=64 where x, Bm, Cm, dt and y are
 // 3.5.  Here a workgroup of four waves walks the sequence of one or two heads
 // (NH) of a group in steps of FQ = 64 positions with the state in registers
-// (fp32), so x is read and y written once and nothing else moves: 2.06 ms ->
-// 0.92 ms there.  The same traffic without the arithmetic takes 0.58 ms, the
+// (fp32), so x is read and y written once and nothing else moves: 2.07 ms ->
+// 0.97 ms there.  The same traffic without the arithmetic takes 0.58 ms, the
 // arithmetic without the stores 0.75: what bounds it is the instructions of
 // the two waves that share a SIMD (VALU issue 41 %, matrix cores 27 % of the
 // time) and their waits on each other.
@@ -683,7 +683,9 @@ __global__ __launch_bounds__(NT, 4) void state_passing_kernel(PassArgs args)
 //    sends more of y through the state, costs no precision: every term of y
 //    is rounded once (the weighted x, or the within-step weight).  Error
 //    against 64 bits at B=2 L=1000 H=512: 1.20e-3 for y and 1.66e-3 for the
-//    states, as the chained functions.
+//    states, as the chained functions.  The rest is clamped, or an infinite
+//    state would leave inf - inf and turn the infinities of y into NaN (B=64
+//    L=2048 948 -> 966 us, B=1 L=1000 30.6 -> 30.9).
 //  * A step reads the C tile once for both that term and the blocks of
 //    C B^T, whose weighted form (bf16, in LDS) the waves exchange; every tile
 //    is dead at the barrier behind it, so that a step has two barriers.
@@ -701,6 +703,7 @@ constexpr int FQ = 64;                    // positions per step
 constexpr int FX_BYTES = FQ * SP * 2;     // one head's x tile
 constexpr int FB_BYTES = FQ * SN * 2;     // B or C tile
 constexpr int FM_BYTES = FQ * FQ * 2;     // one head's weight tile
+constexpr float LO_MAX = 0x1p120f;        // past the low part of any finite state
 
 struct FwdArgs {
     SsdShape s;
@@ -986,7 +989,10 @@ __global__ __launch_bounds__(NT, 2) void ssd_forward_kernel(FwdArgs args)
                         const float v0 = S[pb][2 * kk + (q >> 1)][2 * (q & 1)];
                         const float v1 = S[pb][2 * kk + (q >> 1)][2 * (q & 1) + 1];
                         h4[pb][q] = pack_bf16(v0, v1);
-                        l4[pb][q] = pack_bf16(v0 - bf16_lo(h4[pb][q]), v1 - bf16_hi(h4[pb][q]));
+                        // (an infinite state leaves inf - inf, which the clamp makes finite)
+                        l4[pb][q] = pack_bf16(
+                            __builtin_amdgcn_fmed3f(v0 - bf16_lo(h4[pb][q]), -LO_MAX, LO_MAX),
+                            __builtin_amdgcn_fmed3f(v1 - bf16_hi(h4[pb][q]), -LO_MAX, LO_MAX));
                     }
 #pragma unroll
                 for (int lb = 0; lb < 4; ++lb) {

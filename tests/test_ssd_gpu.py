@@ -272,3 +272,29 @@ def test_forward_one_pass(ta, shape, segments):
     # both paths are within the bound of the same value
     assert float(((y - cy).abs().cpu().numpy() / np.maximum(scale, 1e-30)).max()) <= 2.0 ** -5
     assert float(((final - cfinal).abs().cpu().numpy() / np.maximum(fs, 1e-30)).max()) <= 2.0 ** -6
+
+
+@pytest.mark.parametrize("shape", [(1, 600, 2, 1), (2, 330, 256, 2)], ids=str)
+def test_forward_infinite_state(ta, shape):
+    """An infinite B makes one column of the state infinite: every later
+    position is the infinity of the product's sign, as in the chained
+    functions, not NaN (inf - inf in a split of the state)."""
+    print(f"ssd_forward infinite state {shape}", flush=True)
+    w, inp = problem(shape, seed=5)
+    dx, dB, dC = dev_bf16(inp["x"]), dev_bf16(inp["Bm"]), dev_bf16(inp["Cm"])
+    at, n = 10, 5
+    dB[:, at, :, n] = float("inf")
+    dx[:, at] = torch.where(dx[:, at] < 0, -1.0, 1.0).to(torch.bfloat16)
+    dC[..., n] = torch.where(dC[..., n] < 0, -1.0, 1.0).to(torch.bfloat16)
+    ddt = torch.full((w.B, w.L, w.H), 0.01, device="cuda")   # (no decay underflows)
+    dA = torch.full((w.H,), -1.0, device="cuda")
+    y, final = ta.ssd_forward(dx, ddt, dA, dB, dC)
+    prev, cfinal = ta.ssd_state_passing(ta.ssd_chunk_state(dx, dB, ddt, dA), ddt, dA)
+    cy = ta.ssd_chunk_scan(dx, dC, ta.ssd_bmm_chunk(dC, dB), ddt, dA, prev)
+    sign = dx[:, at].float()[:, None] * dC[..., n].float().repeat_interleave(w.H // w.G, 2)[..., None]
+    want = torch.where(sign > 0, float("inf"), float("-inf"))[:, at:]
+    torch.cuda.synchronize()
+    assert torch.equal(cy[:, at:], want)
+    assert torch.equal(y[:, at:], want)
+    assert torch.isfinite(y[:, :at]).all()
+    assert torch.equal(torch.isinf(final), torch.isinf(cfinal))
