@@ -670,7 +670,7 @@ __global__ __launch_bounds__(NT, 4) void state_passing_kernel(PassArgs args)
 // (fp32), so x is read and y written once and nothing else moves: 2.07 ms ->
 // 0.97 ms there.  The same traffic without the arithmetic takes 0.58 ms, the
 // arithmetic without the stores 0.75: what bounds it is the instructions of
-// the two waves that share a SIMD (VALU issue 41 %, matrix cores 27 % of the
+// the two waves that share a SIMD (VALU issue 46 %, matrix cores 28 % of the
 // time) and their waits on each other.
 //  * A head's state S^T[n][p] and y^T[p][l] are split over 4 / NH waves, 16 NH
 //    head dims each (16 x 16 accumulator blocks, lane = dim p of the state,
