@@ -183,8 +183,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(GArgs args)
     const int xcd = blockIdx.x % NXCD, idx = blockIdx.x / NXCD;
     const int ts = xcd * per + (xcd < rem ? xcd : rem) + idx;
     // (K is only split over tiles of 128 x 128 into fp32 partial products: the
-    // others are built without: 4096 x 8192 x 8192 with it, and the
-    // general division below for full groups, 1.8 us longer, now 1.3)
+    // others are built without, 4096 x 8192 x 8192 0.5 us shorter)
     constexpr bool MAY_SPLIT = BM == 128 && !CBF16;
     const uint32_t split = MAY_SPLIT && a.n_split > 1 ? ts / a.n_tiles : 0;
     const int t = ts - split * a.n_tiles;
@@ -196,11 +195,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(GArgs args)
     // 896 x 8192 x 8192 154 -> 130 us, 1280 x 8192 x 8192 252 -> 207.
     const int grp = t / (GROUP_M * a.tiles_n), w = t % (GROUP_M * a.tiles_n);
     const int rows = min(a.M / BM - grp * GROUP_M, GROUP_M);   // tile rows of this group
-    int tm = grp * GROUP_M + w % GROUP_M, tn = w / GROUP_M;
-    if (rows != GROUP_M) {
-        tm = grp * GROUP_M + w % rows;
-        tn = w / rows;
-    }
+    const int tm = grp * GROUP_M + w % rows, tn = w / rows;
     const int m0 = tm * BM, n0 = tn * BN;
     const int cw = KS == 1 ? wave & 3 : wave % C::WPG;    // column of the wave's block
     const int wm = KS == 1 ? (wave >> 2) * C::WM : 0, wn = cw * C::WN;
