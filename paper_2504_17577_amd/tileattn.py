@@ -3,6 +3,11 @@ include/tileattn.h, under the same names, with torch tensors marshalled to
 device pointers.  Every step of attention runs in the HIP library; this module
 only checks dtypes/devices, allocates outputs with torch and passes pointers
 and torch's current stream.  If the library is not built, every call raises.
+
+With ``stream`` given, inputs and outputs are the caller's to order: an output
+that a call allocates is memory of the current stream, so ``stream`` waits for
+that stream first, as for any tensor of torch's.  Workspaces that a call
+allocates for itself need no such wait.
 """
 from __future__ import annotations
 
@@ -224,14 +229,21 @@ def _stream_handle(stream, t):
     return torch._C._cuda_getCurrentRawStream(t.get_device()) if stream is None else stream.cuda_stream
 
 
+def _scratch(shape, dtype, t, stream):
+    """Memory on t's device for a launch on ``stream`` (None: the current one),
+    freed by its caller when the call returns.  It is allocated with that
+    stream current: the allocator hands out and takes back a block in the
+    order of the stream it was allocated on, so a block of the current
+    stream's could still be in use by work queued there, or be given to such
+    work, while the launch on ``stream`` runs."""
+    if stream is None:
+        return torch.empty(shape, dtype=dtype, device=t.device)
+    with torch.cuda.stream(stream):
+        return torch.empty(shape, dtype=dtype, device=t.device)
+
+
 def _workspace(need, t, stream):
-    """A workspace freed by its caller when the call returns; used on a stream
-    other than the current one, the allocator must not hand the block to other
-    work before the launch there has finished."""
-    ws = torch.empty(max(need, 16), dtype=torch.uint8, device=t.device)
-    if stream is not None:
-        ws.record_stream(stream)
-    return ws
+    return _scratch((max(need, 16),), torch.uint8, t, stream)
 
 
 def _attn(q, k, v, causal, scale, out, lse, stream, o_dtype, raw):
@@ -645,9 +657,13 @@ def ssd_forward(x, dt, A, Bm, Cm, D=None, stream=None, num_segments: int | None 
     if D is not None:
         _ssd_check("D", D, torch.float32, (H,))
     if H > 1 << 17 or L > 1 << 30:   # outside the one-pass call: the functions chained
-        states = ssd_chunk_state(x, Bm, dt, A, stream=stream)
-        prev, final = ssd_state_passing(states, dt, A, stream=stream)
-        cb = ssd_bmm_chunk(Cm, Bm, stream=stream)
+        nc = -(-L // SSD_CHUNK)
+        states = _scratch((Bsz, nc, H, P, N), torch.float32, x, stream)
+        prev = _scratch((Bsz, nc, H, P, N), torch.float32, x, stream)
+        cb = _scratch((Bsz, nc, G, SSD_CHUNK, SSD_CHUNK), torch.float32, x, stream)
+        ssd_chunk_state(x, Bm, dt, A, out=states, stream=stream)
+        _, final = ssd_state_passing(states, dt, A, prev=prev, stream=stream)
+        ssd_bmm_chunk(Cm, Bm, out=cb, stream=stream)
         return ssd_chunk_scan(x, Cm, cb, dt, A, prev, D, stream=stream), final
     if num_segments is None:
         num_segments = ssd_segment_heuristic(Bsz, L, H)

@@ -241,3 +241,32 @@ def test_gemm_split_full_compare(ta, shape, splits):
     check(f"gemm split {shape}", c, a, b)
     assert torch.equal(c, c2)
     assert torch.equal(c16.view(torch.int16), c.to(torch.bfloat16).view(torch.int16))
+
+
+def test_gemm_split_on_a_side_stream_leaves_pending_memory_alone(ta):
+    """A block that work queued on the current stream still writes, freed there
+    before the call, must not become the call's workspace on another stream:
+    the current stream's pool hands such blocks out in its own order only."""
+    M, N, K = 384, 4224, 8256
+    n = ta.gemm_split_heuristic(M, N, K)
+    assert n > 1
+    a, b = gen.random_gemm_problem(M, N, K, seed=3)
+    da, db = dev(a), dev(b)
+    ref = ta.gemm_bf16(da, db)
+    outs = [torch.empty_like(ref) for _ in range(8)]
+    slow = torch.zeros(1 << 27, device="cuda")
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    block = torch.empty(ta.gemm_split_workspace_bytes(M, N, n), dtype=torch.uint8, device="cuda")
+    where = block.data_ptr()
+    for _ in range(8):
+        slow.add_(1.0)
+    block.fill_(0xFF)            # queued behind them (fp32 NaN)
+    del block
+    for c in outs:
+        ta.gemm_bf16(da, db, out=c, stream=s)
+    again = torch.empty(ta.gemm_split_workspace_bytes(M, N, n), dtype=torch.uint8, device="cuda")
+    assert again.data_ptr() == where, "the current stream's block went to the call"
+    torch.cuda.synchronize()
+    assert all(torch.equal(c, ref) for c in outs)
