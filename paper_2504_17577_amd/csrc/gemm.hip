@@ -790,13 +790,20 @@ ta_status gemm_split_workspace_bytes(int M, int N, int num_splits, size_t *bytes
 // The split count with the smallest estimate, if that is a tenth and 3 us
 // (the second launch and the workspace) under the unsplit one:
 //   K steps per range x us per step (0.5 with at most a quarter of the CUs at
-//   work, 0.55 up to one workgroup per CU, 0.85 for two) + 6
+//   work, 0.55 up to one workgroup per CU, from there 0.8 rising to 1.05 with
+//   two on each) + 6
 //   + for more than one range 4 + 8 M N S bytes at 4.5 TB/s.
-// Within 10 % of what was measured over 128-3072 x 384-4224 x 192-28672 (us,
-// unsplit | by S): 384 x 4224 x 8256 74 | 2: 48, 4: 46, 5: 42; 512 x 4096 x 4096
-// 42 | 2: 34, 4: 37; 128 x 4096 x 4096 38 | 2: 26, 4: 21, 8: 21; 128 x 1024 x 8192
-// 61 | 8: 18, 16: 18, 32: 21; 256 x 1024 x 28672 244 | 8: 45, 16: 33; 1024 x 1024 x
-// 1024 14 | 2: 18; 2048 x 1024 x 2048 23 | 2: 24; 3072 x 1024 x 8192 77 | 2: 74.
+// The order of its values matters, not their size (0.6 to 1.5 times the
+// measured ones): over 490 products of 1 to 256 tiles, K 256-28672, no count it
+// picks is more than 1 % slower than the unsplit product.  With 0.85 for every
+// grid of two per CU it split some that nearly fill the CUs (us, unsplit | in
+// two, K = 28672: 512 x 8192 263 | 273, 256 x 16384 290 | 309, 1024 x 3840 248 |
+// 261; K = 16384: 128 x 24576 188 | 201, 256 x 12800 168 | 175).
+// Measured (us, unsplit | by S, bf16 C): 384 x 4224 x 8256 61 | 2: 42, 4: 38, 5: 37;
+// 512 x 4096 x 8256 60 | 4: 43; 512 x 4224 x 4096 34 | 2: 34, 3: 30; 128 x 4224 x
+// 4096 34 | 2: 24, 4: 19, 6: 18, 8: 19; 128 x 1024 x 8256 61 | 8: 18, 16: 18, 32: 21;
+// 256 x 1024 x 28672 196 | 8: 34, 16: 29; 1024 x 1024 x 1024 14 | 2: 17; 2048 x 1024
+// x 2048 21 | 2: 23.
 ta_status gemm_split_heuristic(int M, int N, int K, int *num_splits)
 {
     if (!num_splits)
@@ -813,7 +820,7 @@ ta_status gemm_split_heuristic(int M, int N, int K, int *num_splits)
         const int64_t wg = tiles * sp;
         if (sp == 1 && wg > 256)
             break;
-        const double per_step = wg <= 64 ? 0.5 : wg <= 256 ? 0.55 : 0.85;
+        const double per_step = wg <= 64 ? 0.5 : wg <= 256 ? 0.55 : 0.8 + 0.25 * (wg - 256) / 256;
         double t = (steps + sp - 1) / sp * per_step + 6;
         if (sp > 1)
             t += 4 + 8.0 * M * N * sp / 4.5e6;

@@ -351,6 +351,14 @@ def test_gemm_split_workspace_and_heuristic():
     assert ta.gemm_split_heuristic(4096, 1024, 8192) == 1 and ta.gemm_split_heuristic(1024, 1024, 1024) == 1
 
 
+@pytest.mark.parametrize("M,N,K", [(512, 8192, 28672), (256, 16384, 28672), (2048, 2048, 1 << 17),
+                                   (1024, 3840, 28672), (256, 12800, 16384), (128, 24576, 28672)])
+def test_gemm_split_heuristic_leaves_nearly_full_grids_unsplit(M, N, K):
+    """Products whose tiles nearly fill the CUs were measured slower in two
+    ranges, whose workgroups then share CUs."""
+    assert ta.gemm_split_heuristic(M, N, K) == 1
+
+
 def test_gemv_split_workspace_and_heuristic():
     assert ta.gemv_split_workspace_bytes(9216, 7) == 7 * 9216 * 4
     assert ta.gemv_split_workspace_bytes(9216, 1) == 0
