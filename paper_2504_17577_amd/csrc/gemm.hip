@@ -156,7 +156,10 @@ struct Cfg {
 // flight during the MFMAs) or a ring of three or four (ST - 1 tiles in
 // flight) for grids of at most one workgroup per CU, where no other
 // workgroup's MFMAs cover the wait for a tile.
-template <int BM, int BN, int ST, int KS, int MF, bool CBF16>
+// SPLIT: C is the fp32 partial products of a.n_split K ranges.  A kernel of its
+// own: the range arithmetic in the unsplit one cost 0.5 us (1024 x 8192 x 192,
+// fp32 C, 11.6 us with it, 11.1 without).
+template <int BM, int BN, int ST, int KS, int MF, bool CBF16, bool SPLIT>
 __global__ __launch_bounds__(NT, 2) void gemm_kernel(GArgs args)
 {
     using C = Cfg<BM, BN, KS, MF>;
@@ -182,10 +185,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(GArgs args)
     const int per = a.n_wg / NXCD, rem = a.n_wg % NXCD;
     const int xcd = blockIdx.x % NXCD, idx = blockIdx.x / NXCD;
     const int ts = xcd * per + (xcd < rem ? xcd : rem) + idx;
-    // (K is only split over tiles of 128 x 128 into fp32 partial products: the
-    // others are built without, 4096 x 8192 x 8192 0.5 us shorter)
-    constexpr bool MAY_SPLIT = BM == 128 && !CBF16;
-    const uint32_t split = MAY_SPLIT && a.n_split > 1 ? ts / a.n_tiles : 0;
+    const uint32_t split = SPLIT ? ts / a.n_tiles : 0;
     const int t = ts - split * a.n_tiles;
     // grouped order: GROUP_M consecutive logical tiles walk down a column of
     // tiles before moving right (fewer in a last group of fewer rows), so the
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(GArgs args)
     // 2^30 and N >= 128, so the products fit 32 bits)
     const uint32_t kt_all = a.K / BK;
     int kt_lo = 0, n_kt = kt_all;
-    if (MAY_SPLIT && a.n_split > 1) {
+    if (SPLIT) {
         kt_lo = kt_all * split / a.n_split;
         n_kt = kt_all * (split + 1) / a.n_split - kt_lo;
     }
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(GArgs args)
 
     // epilogue: lane holds column wn + MF j + col, rows wm + MF i +
     // 8(r/4) + 4half + r%4 (MF = 32) or 4half + r (MF = 16) of the tile
-    const size_t c0 = CBF16 ? 0 : (size_t)split * a.M * a.N;
+    const size_t c0 = SPLIT ? (size_t)split * a.M * a.N : 0;
 #pragma unroll
     for (int i = 0; i < C::FM; ++i)
 #pragma unroll
@@ -631,17 +631,31 @@ bool overlaps(const void *p, size_t pn, const void *q, size_t qn)
 // MFMA form holds a higher clock than 32 x 32 x 16 (M5 1314 -> 1346-1359,
 // M1 1274-1297 -> 1333-1348, M4 1150 -> 1177 TFLOP/s); four groups share a
 // K step of 64 as 16-wide k-steps, so their tiles keep 32 x 32 blocks.
+// rows of the MFMA blocks whose k-steps KS groups divide
+constexpr int mfma_rows(int KS) { return (BK / 32) % KS == 0 ? 16 : 32; }
+
 template <int BM, int BN, int ST, int KS>
 hipError_t launch(GArgs &a, bool c_bf16, hipStream_t s)
 {
-    constexpr int MF = (BK / 32) % KS == 0 ? 16 : 32;
+    constexpr int MF = mfma_rows(KS);
     a.tiles_n = a.N / BN;
     a.n_tiles = (a.M / BM) * a.tiles_n;
     a.n_wg = a.n_tiles * a.n_split;
     if (c_bf16)
-        hipLaunchKernelGGL((gemm_kernel<BM, BN, ST, KS, MF, true>), dim3(a.n_wg), dim3(NT), 0, s, a);
+        hipLaunchKernelGGL((gemm_kernel<BM, BN, ST, KS, MF, true, false>), dim3(a.n_wg), dim3(NT), 0, s, a);
     else
-        hipLaunchKernelGGL((gemm_kernel<BM, BN, ST, KS, MF, false>), dim3(a.n_wg), dim3(NT), 0, s, a);
+        hipLaunchKernelGGL((gemm_kernel<BM, BN, ST, KS, MF, false, false>), dim3(a.n_wg), dim3(NT), 0, s, a);
+    return hipGetLastError();
+}
+
+// the partial products of a.n_split > 1 ranges
+template <int ST, int KS>
+hipError_t launch_split(GArgs &a, hipStream_t s)
+{
+    a.tiles_n = a.N / 128;
+    a.n_tiles = (a.M / 128) * a.tiles_n;
+    a.n_wg = a.n_tiles * a.n_split;
+    hipLaunchKernelGGL((gemm_kernel<128, 128, ST, KS, mfma_rows(KS), false, true>), dim3(a.n_wg), dim3(NT), 0, s, a);
     return hipGetLastError();
 }
 
@@ -763,8 +777,8 @@ ta_status gemm_bf16_split(const void *A, const void *B, void *C, int c_bf16, int
     hipStream_t s = (hipStream_t)stream;
     // one workgroup per CU: the four-stage ring, else two stages and two
     // workgroups per CU (as gemm_bf16)
-    hipError_t e = mn / (128 * 128) * num_splits <= 256 ? launch<128, 128, 4, 4>(a, false, s)
-                                                        : launch<128, 128, 2, 2>(a, false, s);
+    hipError_t e = mn / (128 * 128) * num_splits <= 256 ? launch_split<4, 4>(a, s)
+                                                        : launch_split<2, 2>(a, s);
     if (e != hipSuccess)
         return TA_ERR_LAUNCH;
     const dim3 grid((unsigned)(mn / 1024));
