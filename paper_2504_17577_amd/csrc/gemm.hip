@@ -195,7 +195,10 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(GArgs args)
     // 896 x 8192 x 8192 154 -> 130 us, 1280 x 8192 x 8192 252 -> 207.
     const int grp = t / (GROUP_M * a.tiles_n), w = t % (GROUP_M * a.tiles_n);
     const int rows = min(a.M / BM - grp * GROUP_M, GROUP_M);   // tile rows of this group
-    const int tm = grp * GROUP_M + w % rows, tn = w / rows;
+    // (w / rows without a division: rows is 1, 2, 3 or 4)
+    static_assert(GROUP_M == 4, "the quotient by 1 .. GROUP_M");
+    const int tn = rows == 3 ? (int)(((uint64_t)(uint32_t)w * 0xAAAAAAABu) >> 33) : w >> (rows >> 1);
+    const int tm = grp * GROUP_M + w - tn * rows;
     const int m0 = tm * BM, n0 = tn * BN;
     const int cw = KS == 1 ? wave & 3 : wave % C::WPG;    // column of the wave's block
     const int wm = KS == 1 ? (wave >> 2) * C::WM : 0, wn = cw * C::WN;

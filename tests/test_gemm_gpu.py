@@ -243,6 +243,22 @@ def test_gemm_split_full_compare(ta, shape, splits):
     assert torch.equal(c16.view(torch.int16), c.to(torch.bfloat16).view(torch.int16))
 
 
+@pytest.mark.parametrize("shape", [(384, 640, 64), (640, 384, 64), (768, 896, 128), (896, 640, 64),
+                                   (1408, 1152, 64)], ids=str)
+def test_gemm_tile_order(ta, shape):
+    """Every tile once, with a last group of 1, 2 and 3 tile rows after whole
+    groups of four and alone; unsplit and in two ranges."""
+    M, N, K = shape
+    print(f"gemm tile order {shape}", flush=True)
+    a, b = gen.random_gemm_problem(M, N, K, seed=M + N)
+    da, db = dev(a), dev(b)
+    for splits in (1, K // 64):
+        c = torch.full((M, N), float("nan"), device="cuda")
+        ta.gemm_bf16(da, db, out=c, num_splits=splits)
+        torch.cuda.synchronize()
+        check(f"gemm tile order {shape} {splits}", c, a, b)
+
+
 def test_gemm_split_on_a_side_stream_leaves_pending_memory_alone(ta):
     """A block that work queued on the current stream still writes, freed there
     before the call, must not become the call's workspace on another stream:
