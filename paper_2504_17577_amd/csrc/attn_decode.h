@@ -36,6 +36,8 @@ namespace tileattn_detail {
 // Query rows per key/value head (heads of the group times queries) the
 // decode kernel takes.
 constexpr int DECODE_MAX_ROWS = 16;
+// Workgroups of a decode launch: their threads are counted in 32 bits.
+constexpr int64_t DECODE_MAX_WG = (1ll << 32) / 512 - 1;
 
 struct DecodeArgs {
     const uint16_t *Q, *K, *V;
@@ -65,6 +67,7 @@ typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 
 constexpr int NW = 8;                 // waves per workgroup
 constexpr int NT = 64 * NW;
+static_assert(DECODE_MAX_WG * NT < (1ll << 32), "threads of a launch");
 constexpr int RING = 2;               // a K and a V tile per wave
 constexpr int TILE_BYTES = 8192;
 constexpr int DMA = TILE_BYTES / 1024;   // DMA instructions per tile
@@ -338,7 +341,7 @@ __global__ __launch_bounds__(NT, 1) void attn_decode_kernel(DecodeArgs a)
 
 }  // namespace decode
 
-// D = 64 or 128; rows <= DECODE_MAX_ROWS
+// D = 64 or 128; rows <= DECODE_MAX_ROWS, workgroups <= DECODE_MAX_WG
 inline hipError_t launch_attn_decode(const DecodeArgs &a, int D, bool o_bf16, hipStream_t stream)
 {
     const dim3 grid(a.B * a.Hkv * a.n_split), block(decode::NT);

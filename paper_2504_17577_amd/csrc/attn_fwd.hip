@@ -940,10 +940,12 @@ size_t split_workspace_bytes(int B, int Hq, int Sq, int D, int num_splits)
 // waves of a workgroup: faster than the tiled kernel at every split count
 // (us, tiled -> decode: B=1 Hq=4 Hkv=2 Sk=100 D=64 4.5 -> 3.8; B=2 Hq=8 Hkv=2
 // Sq=3 Sk=1000 17.6 -> 14.5; B=4 Hq=Hkv=32 Sk=3583 74 -> 47; B=16 Hq=64 Hkv=8
-// Sk=1000 75 -> 15).
-bool is_decode(int Hq, int Hkv, int Sq)
+// Sk=1000 75 -> 15).  `wg` counts its workgroups, one per (batch, key/value
+// head, split); the tiled kernel, whose workgroups are smaller, takes the calls
+// that have too many for one launch.
+bool is_decode(int64_t wg, int group, int Sq)
 {
-    return (int64_t)(Hq / Hkv) * Sq <= tileattn_detail::DECODE_MAX_ROWS;
+    return (int64_t)group * Sq <= tileattn_detail::DECODE_MAX_ROWS && wg <= tileattn_detail::DECODE_MAX_WG;
 }
 
 // Validation and launch shared by every entry point.  num_splits == 1 runs
@@ -1032,7 +1034,7 @@ ta_status attn_fwd_any(const void *Q, const void *K, const void *V, void *O, boo
 
     hipStream_t s = (hipStream_t)stream;
     const bool kb = o_bf16 && n_split == 1;   // the attention kernel writes bf16 O itself
-    const bool decode = is_decode(Hq, Hkv, Sq);
+    const bool decode = is_decode((int64_t)B * Hkv * n_split, a.group, Sq);
     const int n_cu = decode ? 0 : current_cu_count();
     const bool small = TA_SMALL_TILES && n_split == 1 && n_cu > 0 &&
                        (2 * n_items <= (int64_t)n_cu ||
@@ -1200,7 +1202,7 @@ ta_status ta_split_heuristic(int B, int Hq, int Hkv, int Sq, int Sk, int D, int 
 ta_status ta_split_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int causal, int *num_splits)
 {
     const ta_status st = ta_split_heuristic(B, Hq, Hkv, Sq, Sk, D, causal, num_splits);
-    if (st != TA_OK || !is_decode(Hq, Hkv, Sq))
+    if (st != TA_OK || !is_decode((int64_t)B * Hkv, Hq / Hkv, Sq))
         return st;
     // one decode workgroup per CU, at least 512 keys each (us by count: B=8
     // Hkv=8 Sk=8191 2: 50, 4: 45, 8: 46; B=1 Hkv=8 Sk=8191 4: 25, 8: 17, 16:
@@ -1210,6 +1212,21 @@ ta_status ta_split_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int causa
     n = n < Sk / 512 ? n : Sk / 512;
     n = n < MAX_SPLITS ? n : MAX_SPLITS;
     *num_splits = n > 1 ? (int)n : 1;
+    return TA_OK;
+}
+
+ta_status ta_decode_route(int B, int Hq, int Hkv, int Sq, int Sk, int D, int num_splits, int *decode)
+{
+    if (!decode)
+        return TA_ERR_NULL_POINTER;
+    if (B < 1 || Hq < 1 || Hkv < 1 || Sq < 1 || Sk < 1 || Hq % Hkv != 0 || num_splits < 1 ||
+        num_splits > MAX_SPLITS)
+        return TA_ERR_INVALID_SHAPE;
+    if (D != 64 && D != 128)
+        return TA_ERR_UNSUPPORTED;
+    int split_tiles, n_split;
+    split_shape(Sk, num_splits, &split_tiles, &n_split);
+    *decode = is_decode((int64_t)B * Hkv * n_split, Hq / Hkv, Sq);
     return TA_OK;
 }
 

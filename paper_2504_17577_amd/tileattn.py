@@ -62,6 +62,8 @@ def lib():
     L.ta_split_heuristic.argtypes = [i, i, i, i, i, i, i, ctypes.POINTER(i)]
     L.ta_split_plan.restype = i
     L.ta_split_plan.argtypes = L.ta_split_heuristic.argtypes
+    L.ta_decode_route.restype = i
+    L.ta_decode_route.argtypes = L.ta_split_heuristic.argtypes
     L.mla_decode.restype = i
     L.mla_decode.argtypes = [p, p, p, p, p, p, i, i, i, i, i, i, ctypes.c_float, i, p,
                              ctypes.c_size_t, p]
@@ -158,6 +160,14 @@ def ta_split_plan(B: int, Hq: int, Hkv: int, Sq: int, Sk: int, D: int, causal: b
     if rc != TA_OK:
         raise TileAttnError(rc, ta_status_string(rc))
     return n.value
+
+
+def ta_decode_route(B: int, Hq: int, Hkv: int, Sq: int, Sk: int, D: int, num_splits: int) -> bool:
+    n = ctypes.c_int()
+    rc = lib().ta_decode_route(B, Hq, Hkv, Sq, Sk, D, num_splits, ctypes.byref(n))
+    if rc != TA_OK:
+        raise TileAttnError(rc, ta_status_string(rc))
+    return bool(n.value)
 
 
 def attn_fwd_split_raw(Q, K, V, O, o_bf16, LSE, B, Hq, Hkv, Sq, Sk, D, causal, scale,

@@ -208,6 +208,19 @@ def test_split_plan_properties(shape):
         assert n == max(1, min(256 // (B * Hkv), Sk // 512, 128))
 
 
+@pytest.mark.parametrize("case,decode", [
+    # (B, Hq, Hkv, Sq, Sk, D, splits): a launch counts its threads in 32 bits,
+    # and a decode workgroup has 512
+    ((1 << 23, 8, 1, 1, 16, 64, 1), False), (((1 << 23) - 1, 8, 1, 1, 16, 64, 1), True),
+    ((1 << 20, 64, 8, 1, 16, 128, 1), False), ((1 << 20, 56, 7, 1, 16, 128, 1), True),
+    ((1 << 17, 8, 1, 1, 64 * 64, 64, 64), False), ((1 << 17, 8, 1, 1, 64 * 63, 64, 64), True),
+    ((1, 17, 1, 1, 4096, 128, 1), False), ((1, 8, 8, 17, 4096, 128, 1), False),
+    ((1, 16, 1, 1, 4096, 128, 1), True), ((8, 32, 8, 1, 8191, 128, 4), True),
+])
+def test_decode_route_limits(case, decode):
+    assert ta.ta_decode_route(*case) == decode
+
+
 # mla_decode: argument errors before any HIP call (fake pointers)
 MQ, MQP, MKV, MKP, MO, ML, MWS = (0x10000000, 0x18000000, 0x20000000, 0x30000000, 0x40000000,
                                   0x50000000, 0x60000000)
