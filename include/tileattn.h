@@ -173,7 +173,9 @@ ta_status ta_split_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int causa
 /* Which kernel the attention entry points run for a call of num_splits splits
  * (1 for attn_fwd and attn_fwd_bf16out), for tests and tools: *decode = 1 for
  * the decode kernel, whose workgroups take all query rows of a key/value head
- * (at most 16), 0 for the tiled one.  No HIP call. */
+ * (at most 16), 0 for the tiled one, also for short keys in large grids of one
+ * or two query heads per key/value head, where it is the faster one.  No HIP
+ * call. */
 ta_status ta_decode_route(int B, int Hq, int Hkv, int Sq, int Sk, int D, int num_splits,
                           int *decode);
 

@@ -937,15 +937,41 @@ size_t split_workspace_bytes(int B, int Hq, int Sq, int D, int num_splits)
 
 // Up to 16 query rows per key/value head run the decode kernel, which reads
 // the head's keys and values once for all of them and spreads them over the
-// waves of a workgroup: faster than the tiled kernel at every split count
-// (us, tiled -> decode: B=1 Hq=4 Hkv=2 Sk=100 D=64 4.5 -> 3.8; B=2 Hq=8 Hkv=2
-// Sq=3 Sk=1000 17.6 -> 14.5; B=4 Hq=Hkv=32 Sk=3583 74 -> 47; B=16 Hq=64 Hkv=8
-// Sk=1000 75 -> 15).  `wg` counts its workgroups, one per (batch, key/value
-// head, split); the tiled kernel, whose workgroups are smaller, takes the calls
-// that have too many for one launch.
-bool is_decode(int64_t wg, int group, int Sq)
+// waves of a workgroup, where that is the faster one.  `wg` counts its
+// workgroups, one per (batch, key/value head, split), of which a CU holds one;
+// a tiled workgroup takes one query head, and a CU holds two or four.
+//  * Up to one workgroup per CU: always (us, tiled -> decode: B=1 Hq=4 Hkv=2
+//    Sk=100 D=64 4.5 -> 3.8; B=4 Hq=Hkv=32 Sk=3583 74 -> 47; B=16 Hq=64 Hkv=8
+//    Sk=1000 75 -> 15), but for a single whole key tile and few query heads,
+//    where the tiled kernel needs no mask (64 heads D=64 3.5 | 3.9).
+//  * More, with three and more query heads per key/value head: always (300
+//    workgroups of three D=64 Sk=64 6.6 -> 6.4, of eight D=128 Sk=2048 343 -> 78).
+//  * More, with one: fill and merge of the rounds overlap nothing, so the keys
+//    have to be many (D=64, tiled | decode: 300 workgroups Sk=64 4.6 | 6.5, 256
+//    8.3 | 7.8, 512 13.3 | 11.6; 2048 workgroups Sk=128 19 | 25, 512 45 | 50, 1024
+//    98 | 85; D=128: 512 workgroups Sk=64 7 | 9, 8192 workgroups Sk=128 0.93, 256
+//    1.04 times as fast; 1536 workgroups Sk=256 0.89, 448 1.08), and at D = 128
+//    a second round of fewer than 64 gains nothing at any length (0.95-1.02).
+//  * More, with two: one key tile at D = 64 is too short (0.82-1.0).
+// And a launch counts its threads in 32 bits: the tiled kernel, whose
+// workgroups are smaller, takes the calls with too many for one launch.
+bool is_decode(int64_t wg, int group, int Sq, int64_t keys, int D)
 {
-    return (int64_t)group * Sq <= tileattn_detail::DECODE_MAX_ROWS && wg <= tileattn_detail::DECODE_MAX_WG;
+    constexpr int64_t CUS = 256;
+    if ((int64_t)group * Sq > tileattn_detail::DECODE_MAX_ROWS || wg > tileattn_detail::DECODE_MAX_WG)
+        return false;
+    if (wg <= CUS)
+        return keys != BN || wg * group > CUS;
+    if (group == 1)
+        return D == 64 ? keys >= (wg <= 2 * CUS ? 448 : 1024) : wg >= CUS + 64 && keys >= 640;
+    return group > 2 || D == 128 || keys > BN;
+}
+
+// the same for the call that split_shape has cut
+bool is_decode(int B, int Hq, int Hkv, int Sq, int Sk, int D, int split_tiles, int n_split)
+{
+    const int64_t keys = (int64_t)split_tiles * BN;
+    return is_decode((int64_t)B * Hkv * n_split, Hq / Hkv, Sq, keys < Sk ? keys : Sk, D);
 }
 
 // Validation and launch shared by every entry point.  num_splits == 1 runs
@@ -1034,7 +1060,7 @@ ta_status attn_fwd_any(const void *Q, const void *K, const void *V, void *O, boo
 
     hipStream_t s = (hipStream_t)stream;
     const bool kb = o_bf16 && n_split == 1;   // the attention kernel writes bf16 O itself
-    const bool decode = is_decode((int64_t)B * Hkv * n_split, a.group, Sq);
+    const bool decode = is_decode(B, Hq, Hkv, Sq, Sk, D, split_tiles, n_split);
     const int n_cu = decode ? 0 : current_cu_count();
     const bool small = TA_SMALL_TILES && n_split == 1 && n_cu > 0 &&
                        (2 * n_items <= (int64_t)n_cu ||
@@ -1202,7 +1228,7 @@ ta_status ta_split_heuristic(int B, int Hq, int Hkv, int Sq, int Sk, int D, int 
 ta_status ta_split_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int causal, int *num_splits)
 {
     const ta_status st = ta_split_heuristic(B, Hq, Hkv, Sq, Sk, D, causal, num_splits);
-    if (st != TA_OK || !is_decode((int64_t)B * Hkv, Hq / Hkv, Sq))
+    if (st != TA_OK || (int64_t)(Hq / Hkv) * Sq > tileattn_detail::DECODE_MAX_ROWS)
         return st;
     // one decode workgroup per CU, at least 512 keys each (us by count: B=8
     // Hkv=8 Sk=8191 2: 50, 4: 45, 8: 46; B=1 Hkv=8 Sk=8191 4: 25, 8: 17, 16:
@@ -1226,7 +1252,7 @@ ta_status ta_decode_route(int B, int Hq, int Hkv, int Sq, int Sk, int D, int num
         return TA_ERR_UNSUPPORTED;
     int split_tiles, n_split;
     split_shape(Sk, num_splits, &split_tiles, &n_split);
-    *decode = is_decode((int64_t)B * Hkv * n_split, Hq / Hkv, Sq);
+    *decode = is_decode(B, Hq, Hkv, Sq, Sk, D, split_tiles, n_split);
     return TA_OK;
 }
 

@@ -221,6 +221,31 @@ def test_decode_route_limits(case, decode):
     assert ta.ta_decode_route(*case) == decode
 
 
+def test_decode_route_by_grid_and_keys():
+    """Where the tiled kernel was measured faster: large grids of short keys
+    with one query head per key/value head, one key tile with two at D = 64,
+    a nearly empty second round at D = 128, a single whole tile in a small
+    grid."""
+    def route(wg, group, Sk, D, Sq=1, splits=1):
+        return ta.ta_decode_route(wg, group, 1, Sq, Sk, D, splits)
+
+    for D in (64, 128):
+        for wg in (1, 100, 256):
+            for group in (1, 2, 16):
+                for Sk in (1, 16, 63, 65, 128, 4096):
+                    assert route(wg, group, Sk, D)
+                assert route(wg, group, 64, D) == (wg * group > 256)
+        for wg in (257, 2048, 32768):
+            assert all(route(wg, group, Sk, D) for group in (3, 4, 16) for Sk in (1, 64, 1000))
+            assert not any(route(wg, 1, Sk, D, Sq) for Sk in (16, 64, 128, 447) for Sq in (1, 16))
+    assert route(300, 1, 448, 64) and not route(513, 1, 1023, 64) and route(513, 1, 1024, 64)
+    assert route(320, 1, 640, 128) and not route(319, 1, 8192, 128) and not route(320, 1, 639, 128)
+    assert not route(300, 2, 64, 64) and route(300, 2, 65, 64) and route(300, 2, 16, 128)
+    # splits count as workgroups, and their keys per split
+    assert route(64, 1, 4096, 64, splits=4) and not route(64, 1, 2048, 64, splits=8)
+    assert route(64, 1, 4096, 64, splits=8)
+
+
 # mla_decode: argument errors before any HIP call (fake pointers)
 MQ, MQP, MKV, MKP, MO, ML, MWS = (0x10000000, 0x18000000, 0x20000000, 0x30000000, 0x40000000,
                                   0x50000000, 0x60000000)

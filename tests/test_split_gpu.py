@@ -184,3 +184,22 @@ def test_decode_rows_against_oracle(ta, case, out_dtype):
     _, lse0 = run_split(ta, q, k, v, causal, 0.0, splits, out_dtype=out_dtype)
     seen = np.array([min(Sk, i + 1 + Sk - Sq) if causal else Sk for i in range(Sq)])
     assert float(np.abs(lse0.cpu().numpy() - np.log(seen)).max()) <= 1e-5
+
+
+@pytest.mark.parametrize("case", [
+    # (B, Hq, Hkv, Sq, Sk, D, causal): both sides of the choice between the
+    # decode and the tiled kernel
+    (4, 8, 8, 1, 64, 64, False), (5, 64, 64, 1, 65, 64, False), (75, 4, 4, 1, 447, 64, True),
+    (75, 4, 4, 1, 448, 64, True), (80, 4, 4, 2, 640, 128, True), (79, 4, 4, 2, 640, 128, True),
+    (150, 4, 2, 3, 64, 64, True), (150, 4, 2, 3, 65, 64, False), (100, 9, 3, 5, 16, 128, True),
+], ids=str)
+def test_decode_route_boundaries(ta, case):
+    B, Hq, Hkv, Sq, Sk, D, causal = case
+    print(f"decode route {case} decode={ta.ta_decode_route(B, Hq, Hkv, Sq, Sk, D, 1)}", flush=True)
+    q, k, v = gen.random_problem(B, Hq, Hkv, Sq, Sk, D, seed=29)
+    ro, rl = oracle.attn_fwd(q, k, v, causal, D ** -0.5)
+    for f in (ta.attn_fwd, ta.attn_fwd_bf16out):
+        o, lse = f(dev(q), dev(k), dev(v), causal=causal)
+        torch.cuda.synchronize()
+        assert float(np.abs(o.float().cpu().numpy() - ro).max()) <= O_TOL
+        assert float(np.abs(lse.cpu().numpy() - rl).max()) <= LSE_TOL
