@@ -165,7 +165,8 @@ ta_status ta_split_heuristic(int B, int Hq, int Hkv, int Sq, int Sk, int D, int 
 /* A split count for attn_fwd_split callers that size the workspace after it:
  * as ta_split_heuristic, but with at most 16 query rows per key/value head
  * (Hq / Hkv * Sq <= 16: a decode step) enough splits for one workgroup per
- * (batch, key/value head, split) on each of 256 CUs, keeping at least 512
+ * (batch, key/value head, split) on each of 256 CUs, and where those are more
+ * than 256 already up to four if they even out the rounds, keeping at least 512
  * keys per split.  No HIP call. */
 ta_status ta_split_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int causal,
                         int *num_splits);

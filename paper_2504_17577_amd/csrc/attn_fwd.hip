@@ -974,6 +974,24 @@ bool is_decode(int B, int Hq, int Hkv, int Sq, int Sk, int D, int split_tiles, i
     return is_decode((int64_t)B * Hkv * n_split, Hq / Hkv, Sq, keys < Sk ? keys : Sk, D);
 }
 
+// An estimate of the decode kernel's time on 256 CUs: rounds of a workgroup on
+// each, 3 us to fill and merge one and 4.6 us a step of its eight waves (131 KB
+// of keys and values) at HBM's rate; a last round of fewer takes 2.2 us a step
+// and more with their number.  (264 workgroups, D = 128, 8191 keys: 224 | 223
+// measured; in two splits 193 | 193, in four 181 | 177.)
+double decode_rounds_us(int64_t wg, int keys, int D)
+{
+    const int steps = (int)(((int64_t)keys * D + 32767) / 32768);
+    const int64_t full = wg / 256;
+    const int rem = (int)(wg % 256);
+    double t = (double)full * (3 + steps * 4.6);
+    if (rem) {
+        const double latency = 2.2 + 0.004 * rem, rate = 0.018 * rem;
+        t += 3 + steps * (latency > rate ? latency : rate);
+    }
+    return t;
+}
+
 // Validation and launch shared by every entry point.  num_splits == 1 runs
 // one kernel writing O and LSE; num_splits > 1 writes per-split partial
 // results into the workspace and merges them with combine_kernel.
@@ -1230,10 +1248,24 @@ ta_status ta_split_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int causa
     const ta_status st = ta_split_heuristic(B, Hq, Hkv, Sq, Sk, D, causal, num_splits);
     if (st != TA_OK || (int64_t)(Hq / Hkv) * Sq > tileattn_detail::DECODE_MAX_ROWS)
         return st;
+    const int64_t wg = (int64_t)B * Hkv;
+    if (wg > 256) {
+        // more workgroups than CUs: up to four splits that even out the rounds
+        const double rows = (double)wg * (Hq / Hkv) * Sq;
+        double best = decode_rounds_us(wg, Sk, D);
+        for (int sp = 2; sp <= 4 && Sk / sp >= 512; ++sp) {
+            const double t = decode_rounds_us(wg * sp, (Sk + sp - 1) / sp, D) + 3.7 +
+                             1.5 * rows * sp * (D + 1) * 4 / 5e6;
+            if (t < 0.97 * best) {
+                best = t;
+                *num_splits = sp;
+            }
+        }
+        return TA_OK;
+    }
     // one decode workgroup per CU, at least 512 keys each (us by count: B=8
     // Hkv=8 Sk=8191 2: 50, 4: 45, 8: 46; B=1 Hkv=8 Sk=8191 4: 25, 8: 17, 16:
     // 14; B=16 Hkv=8 Sk=1000 1: 15, 2: 16)
-    const int64_t wg = (int64_t)B * Hkv;
     int64_t n = 256 / wg;
     n = n < Sk / 512 ? n : Sk / 512;
     n = n < MAX_SPLITS ? n : MAX_SPLITS;

@@ -208,6 +208,19 @@ def test_split_plan_properties(shape):
         assert n == max(1, min(256 // (B * Hkv), Sk // 512, 128))
 
 
+@pytest.mark.parametrize("shape,n", [
+    # one and a bit rounds: splits even them out (us with one split | with n:
+    # 264 workgroups 223 | 177, 288 228 | 187, two full rounds 81 | 83)
+    ((33, 64, 8, 1, 8191, 128), 4), ((9, 32, 32, 1, 8191, 128), 3), ((33, 64, 8, 1, 4100, 64), 2),
+    ((16, 32, 32, 1, 2048, 128), 1), ((33, 64, 8, 1, 600, 128), 1), ((100, 64, 64, 1, 8192, 128), 1),
+    ((1 << 20, 8, 8, 1, 1 << 20, 64), 1),
+])
+def test_split_plan_rounds(shape, n):
+    got = ta.ta_split_plan(*shape, False)
+    assert (got > 1) == (n > 1) and got <= 4 and (got == 1 or shape[4] // got >= 512)
+    assert abs(got - n) <= 1
+
+
 @pytest.mark.parametrize("case,decode", [
     # (B, Hq, Hkv, Sq, Sk, D, splits): a launch counts its threads in 32 bits,
     # and a decode workgroup has 512
