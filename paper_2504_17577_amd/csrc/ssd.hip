@@ -683,9 +683,10 @@ __global__ __launch_bounds__(NT, 4) void state_passing_kernel(PassArgs args)
 //    sends more of y through the state, costs no precision: every term of y
 //    is rounded once (the weighted x, or the within-step weight).  Error
 //    against 64 bits at B=2 L=1000 H=512: 1.20e-3 for y and 1.66e-3 for the
-//    states, as the chained functions.  The rest is clamped, or an infinite
-//    state would leave inf - inf and turn the infinities of y into NaN (B=64
-//    L=2048 948 -> 966 us, B=1 L=1000 30.6 -> 30.9).
+//    states, as the chained functions.  Values of y that this makes NaN (an
+//    infinite state leaves inf - inf) are taken again from the rounded state
+//    alone, behind a test of their sum per step and wave (B=64 L=2048 981 -> 970
+//    us against a clamp of every rest, which let NaN through).
 //  * A step reads the C tile once for both that term and the blocks of
 //    C B^T, whose weighted form (bf16, in LDS) the waves exchange; every tile
 //    is dead at the barrier behind it, so that a step has two barriers.
@@ -703,7 +704,6 @@ constexpr int FQ = 64;                    // positions per step
 constexpr int FX_BYTES = FQ * SP * 2;     // one head's x tile
 constexpr int FB_BYTES = FQ * SN * 2;     // B or C tile
 constexpr int FM_BYTES = FQ * FQ * 2;     // one head's weight tile
-constexpr float LO_MAX = 0x1p120f;        // past the low part of any finite state
 
 struct FwdArgs {
     SsdShape s;
@@ -989,10 +989,7 @@ __global__ __launch_bounds__(NT, 2) void ssd_forward_kernel(FwdArgs args)
                         const float v0 = S[pb][2 * kk + (q >> 1)][2 * (q & 1)];
                         const float v1 = S[pb][2 * kk + (q >> 1)][2 * (q & 1) + 1];
                         h4[pb][q] = pack_bf16(v0, v1);
-                        // (an infinite state leaves inf - inf, which the clamp makes finite)
-                        l4[pb][q] = pack_bf16(
-                            __builtin_amdgcn_fmed3f(v0 - bf16_lo(h4[pb][q]), -LO_MAX, LO_MAX),
-                            __builtin_amdgcn_fmed3f(v1 - bf16_hi(h4[pb][q]), -LO_MAX, LO_MAX));
+                        l4[pb][q] = pack_bf16(v0 - bf16_lo(h4[pb][q]), v1 - bf16_hi(h4[pb][q]));
                     }
 #pragma unroll
                 for (int lb = 0; lb < 4; ++lb) {
@@ -1003,6 +1000,45 @@ __global__ __launch_bounds__(NT, 2) void ssd_forward_kernel(FwdArgs args)
                         y[pb][lb] = mfma16(__builtin_bit_cast(bf16x8, h4[pb]), cv, y[pb][lb]);
                         y[pb][lb] = mfma16(__builtin_bit_cast(bf16x8, l4[pb]), cv, y[pb][lb]);
                     }
+                }
+            }
+            // A state that is infinite, or rounds to it, has no finite low part
+            // (inf - inf), and low parts of either sign meet an infinite C: NaN
+            // where the state rounded once gives an infinity.  Such values are
+            // taken again from the high parts alone, as the chained functions
+            // have them.
+            float nan = 0.f;
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                for (int lb = 0; lb < 4; ++lb)
+                    nan += (y[pb][lb][0] + y[pb][lb][1]) + (y[pb][lb][2] + y[pb][lb][3]);
+            if (__builtin_amdgcn_ballot_w64(nan != nan)) {
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) {
+                    f32x4 yh[4];
+#pragma unroll
+                    for (int lb = 0; lb < 4; ++lb)
+                        yh[lb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int kk = 0; kk < 4; ++kk) {
+                        // (opaque copies, or the high parts above stay in
+                        // registers for this)
+                        f32x4 s0 = S[pb][2 * kk], s1 = S[pb][2 * kk + 1];
+                        asm volatile("" : "+v"(s0), "+v"(s1));
+                        const u32x4 h = {pack_bf16(s0[0], s0[1]), pack_bf16(s0[2], s0[3]),
+                                         pack_bf16(s1[0], s1[1]), pack_bf16(s1[2], s1[3])};
+#pragma unroll
+                        for (int lb = 0; lb < 4; ++lb) {
+                            const bf16x8 cv = *(const bf16x8 *)(ct + lb * (16 * SN * 2) + (crd ^ (64 * kk)));
+                            yh[lb] = mfma16(__builtin_bit_cast(bf16x8, h), cv, yh[lb]);
+                        }
+                    }
+#pragma unroll
+                    for (int lb = 0; lb < 4; ++lb)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            y[pb][lb][r] = y[pb][lb][r] != y[pb][lb][r] ? yh[lb][r] : y[pb][lb][r];
                 }
             }
             // The within-step weights (C_l . B_s) exp(a_l - a_s) dt_s.  Lane:

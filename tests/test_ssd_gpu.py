@@ -298,3 +298,39 @@ def test_forward_infinite_state(ta, shape):
     assert torch.equal(y[:, at:], want)
     assert torch.isfinite(y[:, :at]).all()
     assert torch.equal(torch.isinf(final), torch.isinf(cfinal))
+
+
+def infinite_state_problem(shape, c, b, dt, A):
+    """One column n of the state infinite from position 10 on, every x and C
+    that meets it of size 1 and ``c``: y is the infinity of the product's sign
+    from there on.  Returns the inputs of ssd_forward and those y."""
+    w, inp = problem(shape, seed=7)
+    dx, dB, dC = dev_bf16(inp["x"]), dev_bf16(inp["Bm"]), dev_bf16(inp["Cm"])
+    at, n = 10, 5
+    dB[:, at, :, n] = b
+    dx[:, at] = torch.where(dx[:, at] < 0, -1.0, 1.0).to(torch.bfloat16)
+    dC[..., n] = torch.where(dC[..., n] < 0, -c, c).to(torch.bfloat16)
+    ddt = torch.full((w.B, w.L, w.H), dt, device="cuda")
+    dA = torch.full((w.H,), A, device="cuda")
+    sign = dx[:, at].float()[:, None] * dC[..., n].float().repeat_interleave(w.H // w.G, 2)[..., None] * b
+    return (dx, ddt, dA, dB, dC), torch.where(sign > 0, float("inf"), float("-inf"))[:, at:], at
+
+
+def chained(ta, dx, ddt, dA, dB, dC):
+    prev, final = ta.ssd_state_passing(ta.ssd_chunk_state(dx, dB, ddt, dA), ddt, dA)
+    return ta.ssd_chunk_scan(dx, dC, ta.ssd_bmm_chunk(dC, dB), ddt, dA, prev), final
+
+
+@pytest.mark.parametrize("b", [float("inf"), float("-inf")])
+@pytest.mark.parametrize("shape", [(1, 600, 2, 1), (2, 330, 256, 2)], ids=str)
+def test_forward_infinite_state_and_large_c(ta, shape, b):
+    """The low part of an infinite state must not meet C at all: any finite
+    stand-in of the other sign overflows against a large one, to NaN."""
+    print(f"ssd_forward infinite state {shape} {b}, C = 512", flush=True)
+    args, want, at = infinite_state_problem(shape, 512.0, b, 0.01, -1.0)
+    y, final = ta.ssd_forward(*args)
+    cy, cfinal = chained(ta, *args)
+    torch.cuda.synchronize()
+    assert torch.equal(cy[:, at:], want) and torch.equal(y[:, at:], want)
+    assert torch.isfinite(y[:, :at]).all()
+    assert torch.equal(torch.isinf(final), torch.isinf(cfinal)) and not torch.isnan(final).any()
