@@ -372,6 +372,10 @@ ta_status ssd_chunk_scan(const void *x, const void *Cm, const float *cb, const f
  * states of the four functions in memory (each workgroup walks a head's
  * sequence with the state in registers).  Same inputs, outputs and precision
  * as the four chained: bf16 operands of the contractions, fp32 sums and state.
+ * What depends on an infinite or NaN input is not finite, as there; an infinite
+ * state gives the infinities of its products with C, and an infinite x (infinite
+ * states of both signs) NaN after the step of 64 positions it is in, where the
+ * chunk functions give NaN after its chunk of 256.
  *
  *   out          device, fp32 [batch, L, nheads, headdim]        written
  *   final_states device, fp32 [batch, nheads, headdim, dstate], or NULL

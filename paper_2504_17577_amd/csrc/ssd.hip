@@ -918,7 +918,15 @@ __global__ __launch_bounds__(NT, 2) void ssd_forward_kernel(FwdArgs args)
             for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
-                    S[pb][i] = S[pb][i] * dec + sp[(pb * 8 + i) * 64];
+                {
+                    f32x4 &st = S[pb][i];
+                    const f32x4 add = sp[(pb * 8 + i) * 64];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        // (a segment's decay may underflow where that of each
+                        // of its steps does not: an infinity stays one)
+                        st[r] = fabsf(st[r]) == INFINITY ? st[r] + add[r] : __builtin_fmaf(st[r], dec, add[r]);
+                }
         }
     }
 

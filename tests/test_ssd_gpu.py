@@ -334,3 +334,21 @@ def test_forward_infinite_state_and_large_c(ta, shape, b):
     assert torch.equal(cy[:, at:], want) and torch.equal(y[:, at:], want)
     assert torch.isfinite(y[:, :at]).all()
     assert torch.equal(torch.isinf(final), torch.isinf(cfinal)) and not torch.isnan(final).any()
+
+
+@pytest.mark.parametrize("shape,segments", [((1, 1600, 2, 1), 5), ((2, 1000, 256, 2), 3)], ids=str)
+def test_forward_infinite_state_over_segments(ta, shape, segments):
+    """A segment of 320 or more positions whose decay underflows fp32, while that
+    of a chunk of 256 does not (2^-124): the infinite state is carried past it,
+    as in one walk and in the chained functions."""
+    print(f"ssd_forward infinite state {shape} in {segments} segments", flush=True)
+    args, want, at = infinite_state_problem(shape, 1.0, float("inf"), 0.0335, -10.0)
+    y1, final1 = ta.ssd_forward(*args, num_segments=1)
+    y, final = ta.ssd_forward(*args, num_segments=segments)
+    cy, cfinal = chained(ta, *args)
+    torch.cuda.synchronize()
+    for v in (cy, y1, y):
+        assert torch.equal(v[:, at:], want)
+    assert torch.isfinite(y[:, :at]).all()
+    for f in (final1, final):
+        assert torch.equal(torch.isinf(f), torch.isinf(cfinal)) and not torch.isnan(f).any()
