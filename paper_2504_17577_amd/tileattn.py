@@ -15,7 +15,10 @@ import ctypes
 import math
 import os
 
-import torch
+try:
+    import torch
+except ImportError:   # the host helpers and the *_raw calls do without it
+    torch = None
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(PKG, "libtileattn.so")

@@ -1,6 +1,9 @@
 """The binding's host logic, on the CPU: stand-ins for GPU tensors and streams,
 and for the C calls (recorded, not made)."""
 import contextlib
+import os
+import subprocess
+import sys
 
 import pytest
 
@@ -126,3 +129,15 @@ def test_scratch_is_allocated_on_the_launch_stream(fake, name, side):
     outputs = {"ssd": 2, "ssd_chained": 2}.get(name, 0)
     assert [x.stream for x in fake.made].count(s) == (n if side else n + outputs)
     assert len(fake.made) == n + outputs
+
+
+def test_module_without_torch():
+    """The host helpers and the *_raw calls take integers only: the module
+    imports and serves them where torch is not installed."""
+    code = ("import sys; sys.modules['torch'] = None\n"
+            "from paper_2504_17577_amd import tileattn as ta\n"
+            "assert ta.ta_split_workspace_bytes(2, 3, 100, 128, 4) == 4 * 2 * 3 * 100 * 129 * 4\n"
+            "assert ta.gemm_bf16_raw(0, 0, 0, False, 128, 128, 64, None) == 1\n")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
