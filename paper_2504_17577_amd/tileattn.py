@@ -579,7 +579,7 @@ def ssd_chunk_state(x, Bm, dt, A, out=None, stream=None):
     with _one_device(x, Bm, dt, A, out):
         _ssd_raise(lib().ssd_chunk_state(x.data_ptr(), Bm.data_ptr(), dt.data_ptr(), A.data_ptr(),
                                          out.data_ptr(), Bsz, L, H, G, P, N, SSD_CHUNK,
-                                         _stream_handle(stream, x)))
+                                         _stream_handle(stream or None, x)))
     return out
 
 
@@ -602,7 +602,7 @@ def ssd_state_passing(states, dt, A, prev=None, final=None, stream=None):
     with _one_device(states, dt, A, prev, final):
         _ssd_raise(lib().ssd_state_passing(states.data_ptr(), dt.data_ptr(), A.data_ptr(),
                                            prev.data_ptr(), final.data_ptr(), Bsz, L, H, P, N,
-                                           SSD_CHUNK, _stream_handle(stream, states)))
+                                           SSD_CHUNK, _stream_handle(stream or None, states)))
     return prev, final
 
 
@@ -617,7 +617,7 @@ def ssd_bmm_chunk(Cm, Bm, out=None, stream=None):
     _ssd_check("out", out, torch.float32, (Bsz, nc, G, SSD_CHUNK, SSD_CHUNK))
     with _one_device(Cm, Bm, out):
         _ssd_raise(lib().ssd_bmm_chunk(Cm.data_ptr(), Bm.data_ptr(), out.data_ptr(), Bsz, L, G, N,
-                                       SSD_CHUNK, _stream_handle(stream, Cm)))
+                                       SSD_CHUNK, _stream_handle(stream or None, Cm)))
     return out
 
 
@@ -639,7 +639,7 @@ def ssd_chunk_scan(x, Cm, cb, dt, A, prev_states, D=None, out=None, stream=None)
         _ssd_raise(lib().ssd_chunk_scan(x.data_ptr(), Cm.data_ptr(), cb.data_ptr(), dt.data_ptr(),
                                         A.data_ptr(), prev_states.data_ptr(),
                                         D.data_ptr() if D is not None else None, out.data_ptr(),
-                                        Bsz, L, H, G, P, N, SSD_CHUNK, _stream_handle(stream, x)))
+                                        Bsz, L, H, G, P, N, SSD_CHUNK, _stream_handle(stream or None, x)))
     return out
 
 
@@ -671,9 +671,9 @@ def ssd_forward(x, dt, A, Bm, Cm, D=None, stream=None, num_segments: int | None 
         _ssd_check("D", D, torch.float32, (H,))
     if H > 1 << 17 or L > 1 << 30:   # outside the one-pass call: the functions chained
         nc = -(-L // SSD_CHUNK)
-        states = _scratch((Bsz, nc, H, P, N), torch.float32, x, stream)
-        prev = _scratch((Bsz, nc, H, P, N), torch.float32, x, stream)
-        cb = _scratch((Bsz, nc, G, SSD_CHUNK, SSD_CHUNK), torch.float32, x, stream)
+        states = _scratch((Bsz, nc, H, P, N), torch.float32, x, stream or None)
+        prev = _scratch((Bsz, nc, H, P, N), torch.float32, x, stream or None)
+        cb = _scratch((Bsz, nc, G, SSD_CHUNK, SSD_CHUNK), torch.float32, x, stream or None)
         ssd_chunk_state(x, Bm, dt, A, out=states, stream=stream)
         _, final = ssd_state_passing(states, dt, A, prev=prev, stream=stream)
         ssd_bmm_chunk(Cm, Bm, out=cb, stream=stream)
@@ -685,11 +685,11 @@ def ssd_forward(x, dt, A, Bm, Cm, D=None, stream=None, num_segments: int | None 
     final = torch.empty((Bsz, H, P, N), dtype=torch.float32, device=x.device)
     ws = None
     if need:
-        ws = _workspace(need, x, stream)
+        ws = _workspace(need, x, stream or None)
     with _one_device(x, Bm, Cm, dt, A, D, out):
         _ssd_raise(lib().ssd_forward(x.data_ptr(), Bm.data_ptr(), Cm.data_ptr(), dt.data_ptr(),
                                      A.data_ptr(), D.data_ptr() if D is not None else None,
                                      out.data_ptr(), final.data_ptr(), Bsz, L, H, G, P, N,
                                      num_segments, ws.data_ptr() if need else None, need,
-                                     _stream_handle(stream, x)))
+                                     _stream_handle(stream or None, x)))
     return out, final

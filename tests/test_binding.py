@@ -131,6 +131,19 @@ def test_scratch_is_allocated_on_the_launch_stream(fake, name, side):
     assert len(fake.made) == n + outputs
 
 
+def test_ssd_calls_take_a_false_stream_as_the_current_one(fake):
+    """stream=0 means the current stream to the SSD functions."""
+    x, dt, A, Bm, Cm = ssd_args(1, 300, 4, 2)
+    st = t(1, 2, 4, 64, 128, dtype=F32)
+    ta.ssd_chunk_state(x, Bm, dt, A, stream=0)
+    ta.ssd_state_passing(st, dt, A, prev=st, stream=0)
+    ta.ssd_bmm_chunk(Cm, Bm, stream=0)
+    ta.ssd_chunk_scan(x, Cm, t(1, 2, 2, 256, 256, dtype=F32), dt, A, st, stream=0)
+    ta.ssd_forward(x, dt, A, Bm, Cm, stream=0)
+    assert [args[-1] for _, args in fake.calls] == [0] * 5
+    assert all(m.stream is None for m in fake.made)
+
+
 def test_module_without_torch():
     """The host helpers and the *_raw calls take integers only: the module
     imports and serves them where torch is not installed."""
