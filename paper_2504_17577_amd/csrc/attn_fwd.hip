@@ -892,7 +892,7 @@ bool misaligned(const void *p) { return ((uintptr_t)p & 15u) != 0; }
 // Integer tile schedule; must agree with the kernel's own loop bounds.
 void schedule(int Sq, int Sk, int causal, int qt, int *n_kv, int *first_masked)
 {
-    const int n_all = (Sk + BN - 1) / BN;
+    const int n_all = (Sk - 1) / BN + 1;
     int n = n_all;
     int fm = (Sk % BN) ? n_all - 1 : n_all;
     if (causal) {
@@ -923,7 +923,7 @@ constexpr int SPLIT_MIN_TILES = 32;
 // tile are dropped).
 void split_shape(int Sk, int num_splits, int *split_tiles, int *n_split)
 {
-    const int n_kv_all = (Sk + BN - 1) / BN;
+    const int n_kv_all = (Sk - 1) / BN + 1;
     const int per = (n_kv_all + num_splits - 1) / num_splits;
     *split_tiles = per;
     *n_split = (n_kv_all + per - 1) / per;
@@ -971,6 +971,8 @@ bool is_decode(int64_t wg, int group, int Sq, int64_t keys, int D)
 bool is_decode(int B, int Hq, int Hkv, int Sq, int Sk, int D, int split_tiles, int n_split)
 {
     const int64_t keys = (int64_t)split_tiles * BN;
+    if ((double)B * Hkv * n_split > tileattn_detail::DECODE_MAX_WG)   // (of any size)
+        return false;
     return is_decode((int64_t)B * Hkv * n_split, Hq / Hkv, Sq, keys < Sk ? keys : Sk, D);
 }
 
@@ -1015,11 +1017,11 @@ ta_status attn_fwd_any(const void *Q, const void *K, const void *V, void *O, boo
     // 32-bit in-kernel offsets are used within one (batch, head) slice only;
     // the grid itself must fit a 32-bit workgroup count
     const int64_t n_qt = ((int64_t)Sq + BM - 1) / BM;
+    if ((int64_t)Sq * D >= (1ll << 31) || (int64_t)Sk * D >= (1ll << 31) ||
+        (double)B * Hq * n_qt * n_split >= 0x1p31 || (double)B * Hq * Sq >= 0x1p31)
+        return TA_ERR_INVALID_SHAPE;
     const int64_t n_items = (int64_t)B * Hq * n_qt * n_split;
     const int64_t n_rows = (int64_t)B * Hq * Sq;
-    if ((int64_t)Sq * D >= (1ll << 31) || (int64_t)Sk * D >= (1ll << 31) ||
-        n_items >= (1ll << 31) || n_rows >= (1ll << 31))
-        return TA_ERR_INVALID_SHAPE;
     if (misaligned(Q) || misaligned(K) || misaligned(V) || misaligned(O) || misaligned(LSE))
         return TA_ERR_MISALIGNED;
     if (!(scale >= 0.f) || !isfinite(scale))
@@ -1230,10 +1232,11 @@ ta_status ta_split_heuristic(int B, int Hq, int Hkv, int Sq, int Sk, int D, int 
         return TA_ERR_INVALID_SHAPE;
     if (D != 64 && D != 128)
         return TA_ERR_UNSUPPORTED;
-    const int64_t n_wg = (int64_t)B * Hq * (((int64_t)Sq + BM - 1) / BM);
-    const int n_kv_all = (Sk + BN - 1) / BN;
+    const double many = (double)B * Hq * (((int64_t)Sq + BM - 1) / BM);   // (of any size)
+    const int n_kv_all = (Sk - 1) / BN + 1;
     int n = 1;
-    if (n_wg < SPLIT_TARGET_WG) {
+    if (many < SPLIT_TARGET_WG) {
+        const int64_t n_wg = (int64_t)many;
         n = (int)((SPLIT_TARGET_WG + n_wg - 1) / n_wg);
         n = n < n_kv_all / SPLIT_MIN_TILES ? n : n_kv_all / SPLIT_MIN_TILES;
         n = n < MAX_SPLITS ? n : MAX_SPLITS;
@@ -1251,10 +1254,13 @@ ta_status ta_split_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int causa
     const int64_t wg = (int64_t)B * Hkv;
     if (wg > 256) {
         // more workgroups than CUs: up to four splits that even out the rounds
+        // (of thousands, nothing is left to even out)
+        if (wg > 1 << 20)
+            return TA_OK;
         const double rows = (double)wg * (Hq / Hkv) * Sq;
         double best = decode_rounds_us(wg, Sk, D);
         for (int sp = 2; sp <= 4 && Sk / sp >= 512; ++sp) {
-            const double t = decode_rounds_us(wg * sp, (Sk + sp - 1) / sp, D) + 3.7 +
+            const double t = decode_rounds_us(wg * sp, (Sk - 1) / sp + 1, D) + 3.7 +
                              1.5 * rows * sp * (D + 1) * 4 / 5e6;
             if (t < 0.97 * best) {
                 best = t;

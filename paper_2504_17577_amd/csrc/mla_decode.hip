@@ -538,7 +538,7 @@ constexpr int MLA_MIN_TILES = 8;
 
 void mla_split_shape(int Skv, int num_splits, int *split_tiles, int *n_split)
 {
-    const int n_tiles = (Skv + BN - 1) / BN;
+    const int n_tiles = (Skv - 1) / BN + 1;
     const int per = (n_tiles + num_splits - 1) / num_splits;
     *split_tiles = per;
     *n_split = (n_tiles + per - 1) / per;
@@ -548,7 +548,7 @@ void mla_split_shape(int Skv, int num_splits, int *split_tiles, int *n_split)
 int heads_per_wg(int64_t n, int g)
 {
     int hb = HB;
-    while (hb > HW && n * ((g + hb / 2 - 1) / (hb / 2)) <= MLA_TARGET_WG)
+    while (hb > HW && n * ((g - 1) / (hb / 2) + 1) <= MLA_TARGET_WG)
         hb /= 2;
     return hb;
 }
@@ -578,16 +578,16 @@ ta_status mla_decode(const void *Q, const void *Q_pe, const void *KV, const void
     int split_tiles, n_split;
     mla_split_shape(Skv, num_splits, &split_tiles, &n_split);
     const int g = H / Hkv;
-    const int n_hblk = (g + HB - 1) / HB;
-    const int64_t n_wg = (int64_t)B * Hkv * n_hblk * n_split;
+    const int n_hblk = (g - 1) / HB + 1;
     // 32-bit in-kernel offsets within one tile; 32-bit grid
-    if (n_wg >= (1ll << 31) || (int64_t)BN * Hkv * DL * 2 >= (1ll << 31))
+    if ((double)B * Hkv * n_hblk * n_split >= 0x1p31 || (int64_t)BN * Hkv * DL * 2 >= (1ll << 31))
         return TA_ERR_INVALID_SHAPE;
     if (misaligned(Q) || misaligned(Q_pe) || misaligned(KV) || misaligned(K_pe) ||
         misaligned(O) || misaligned(LSE))
         return TA_ERR_MISALIGNED;
     if (!(scale >= 0.f) || !isfinite(scale))
         return TA_ERR_INVALID_SCALE;
+    const int64_t n_wg = (int64_t)B * Hkv * n_hblk * n_split;
     const size_t rows = (size_t)B * H;
     const size_t nq = rows * DL, nqr = rows * DR;
     const size_t nkv = (size_t)B * Skv * Hkv * DL, nkr = (size_t)B * Skv * Hkv * DR;
@@ -651,7 +651,7 @@ ta_status mla_decode(const void *Q, const void *Q_pe, const void *KV, const void
     // Skv=1 15 -> 8; B=4 Skv=1999 39 -> 26; B=1 Skv=8192 41 -> 29; B=16
     // Skv=1999 46 -> 34; going on to two workgroups per CU: 34 -> 49.)
     a.hb = heads_per_wg((int64_t)B * Hkv * n_split, g);
-    a.n_hblk = (g + a.hb - 1) / a.hb;
+    a.n_hblk = (g - 1) / a.hb + 1;
     a.n_wg = B * Hkv * a.n_hblk * n_split;
     if (a.n_hblk == 1)
         hipLaunchKernelGGL(mla_decode_kernel<true>, dim3(a.n_wg), dim3(NT), 0, s, a);
@@ -680,10 +680,11 @@ ta_status mla_split_heuristic(int B, int H, int Hkv, int Skv, int *num_splits)
         return TA_ERR_NULL_POINTER;
     if (B < 1 || H < 1 || Hkv < 1 || Skv < 1 || H % Hkv != 0)
         return TA_ERR_INVALID_SHAPE;
-    const int64_t wg = (int64_t)B * Hkv * (((int64_t)(H / Hkv) + HB - 1) / HB);
-    const int n_tiles = (Skv + BN - 1) / BN;
+    const double many = (double)B * Hkv * ((H / Hkv - 1) / HB + 1);   // (of any size)
+    const int n_tiles = (Skv - 1) / BN + 1;
     int n = 1;
-    if (wg < MLA_TARGET_WG) {
+    if (many < MLA_TARGET_WG) {
+        const int64_t wg = (int64_t)many;
         n = (int)((MLA_TARGET_WG + wg - 1) / wg);
         n = n < n_tiles / MLA_MIN_TILES ? n : n_tiles / MLA_MIN_TILES;
         n = n < MAX_SPLITS ? n : MAX_SPLITS;
@@ -710,12 +711,13 @@ ta_status mla_split_plan(int B, int H, int Hkv, int Skv, int *num_splits)
     if (B < 1 || H < 1 || Hkv < 1 || Skv < 1 || H % Hkv != 0)
         return TA_ERR_INVALID_SHAPE;
     const int64_t n = (int64_t)B * Hkv;
-    const int g = H / Hkv, n_tiles = (Skv + BN - 1) / BN;
+    const int g = H / Hkv, n_tiles = (Skv - 1) / BN + 1;
+    const int blocks = (g - 1) / HB + 1;
     double best = 0;
     *num_splits = 1;
-    for (int sp = 1; sp <= MAX_SPLITS && sp <= n_tiles; ++sp) {
-        if (sp > 1 && n * ((g + HB - 1) / HB) * sp > MLA_TARGET_WG)
-            break;
+    if ((double)n * blocks * 2 > MLA_TARGET_WG)   // (of any size)
+        return TA_OK;
+    for (int sp = 1; sp <= MAX_SPLITS && sp <= n_tiles && n * blocks * sp <= MLA_TARGET_WG; ++sp) {
         const int hb = heads_per_wg(n * sp, g);
         const int busy = g < hb ? g : hb;   // heads at work
         const int64_t wg = n * sp * ((g + hb - 1) / hb);

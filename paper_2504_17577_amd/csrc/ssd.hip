@@ -1209,8 +1209,9 @@ ta_status check_shape(int batch, int seqlen, int nheads, int ngroups, int headdi
         return TA_ERR_UNSUPPORTED;
     const int64_t nc = ((int64_t)seqlen + SQ - 1) / SQ;
     // grid sizes and per-tensor element counts within the kernels' index types
-    if ((int64_t)batch * nc * nheads >= (1ll << 31) || (int64_t)batch * nheads * 4 >= (1ll << 31) ||
-        (int64_t)batch * nc * (nheads > ngroups ? nheads : ngroups) * SQ * SQ >= (1ll << 46))
+    // (in floating point: the products of any sizes, exact near the limits)
+    if ((double)batch * nc * nheads >= 0x1p31 || (double)batch * nheads * 4 >= 0x1p31 ||
+        (double)batch * nc * (nheads > ngroups ? nheads : ngroups) * SQ * SQ >= 0x1p46)
         return TA_ERR_INVALID_SHAPE;
     s.B = batch;
     s.L = seqlen;

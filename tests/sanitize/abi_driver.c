@@ -29,6 +29,9 @@ static int failures = 0;
 
 #define P(x) ((void *)(uintptr_t)(x))
 
+#define BIG 2147483647               /* the largest int */
+#define BIG_128 (BIG - 127)          /* the largest multiple of 128 */
+
 /* attn_fwd family: base arguments are valid except where a case changes one */
 typedef struct {
     uintptr_t Q, K, V, O, L, ws;
@@ -262,8 +265,116 @@ static void check_other_validation(void)
            "ssd passing aliasing");
 }
 
+/* gemm_bf16_split and ssd_forward: one argument of a valid call changed */
+static void check_split_gemm_and_forward(void)
+{
+    typedef struct { uintptr_t A, B, C, ws; int M, N, K, splits; size_t ws_bytes; } G;
+    const G g0 = {0x10000000, 0x30000000, 0x50000000, 0x70000000, 256, 256, 256, 3,
+                  (size_t)3 * 256 * 256 * 4};
+    G g;
+#define GEMM(field, value, want)                                                                    \
+    g = g0;                                                                                         \
+    g.field = value;                                                                                \
+    EXPECT(gemm_bf16_split(P(g.A), P(g.B), P(g.C), 1, g.M, g.N, g.K, g.splits, P(g.ws), g.ws_bytes, \
+                           NULL) == want,                                                           \
+           "gemm split " #field "=" #value)
+    GEMM(B, 0, TA_ERR_NULL_POINTER);
+    GEMM(M, 0, TA_ERR_INVALID_SHAPE);
+    GEMM(splits, 65, TA_ERR_INVALID_SHAPE);
+    GEMM(splits, 5, TA_ERR_UNSUPPORTED);
+    GEMM(M, 200, TA_ERR_UNSUPPORTED);
+    GEMM(M, BIG, TA_ERR_UNSUPPORTED);
+    GEMM(N, BIG_128, TA_ERR_INVALID_SHAPE);
+    GEMM(K, BIG_128, TA_ERR_INVALID_SHAPE);
+    GEMM(A, 0x10000008, TA_ERR_MISALIGNED);
+    GEMM(ws, 0x10000000, TA_ERR_ALIASING);
+    GEMM(ws, 0, TA_ERR_WORKSPACE);
+    GEMM(ws_bytes, 1000, TA_ERR_WORKSPACE);
+#undef GEMM
+    typedef struct { uintptr_t x, Bm, Cm, dt, A, D, out, fin, ws; int b, L, H, G, hd, ds, seg; size_t ws_bytes; } S;
+    const S s0 = {0x10000000, 0x11000000, 0x12000000, 0x13000000, 0x14000000, 0x15000000, 0x40000000,
+                  0x30000000, 0x20000000, 1, 300, 4, 2, 64, 128, 2, 1u << 20};
+    S s;
+#define SSD(field, value, want)                                                                  \
+    s = s0;                                                                                      \
+    s.field = value;                                                                             \
+    EXPECT(ssd_forward(P(s.x), P(s.Bm), P(s.Cm), (const float *)P(s.dt), (const float *)P(s.A),  \
+                       (const float *)P(s.D), (float *)P(s.out), (float *)P(s.fin), s.b, s.L,    \
+                       s.H, s.G, s.hd, s.ds, s.seg, P(s.ws), s.ws_bytes, NULL) == want,          \
+           "ssd forward " #field "=" #value)
+    SSD(x, 0, TA_ERR_NULL_POINTER);
+    SSD(L, 0, TA_ERR_INVALID_SHAPE);
+    SSD(seg, 65, TA_ERR_INVALID_SHAPE);
+    SSD(b, BIG, TA_ERR_INVALID_SHAPE);
+    SSD(L, BIG, TA_ERR_INVALID_SHAPE);
+    SSD(H, BIG - 1, TA_ERR_INVALID_SHAPE);
+    SSD(hd, 32, TA_ERR_UNSUPPORTED);
+    SSD(fin, 0x30000004, TA_ERR_MISALIGNED);
+    SSD(out, 0x10000000, TA_ERR_ALIASING);
+    SSD(ws, 0, TA_ERR_WORKSPACE);
+#undef SSD
+    s = s0;
+    s.b = s.L = s.H = s.G = BIG;
+    EXPECT(ssd_forward(P(s.x), P(s.Bm), P(s.Cm), (const float *)P(s.dt), (const float *)P(s.A), NULL,
+                       (float *)P(s.out), NULL, s.b, s.L, s.H, s.G, s.hd, s.ds, 64, P(s.ws),
+                       s.ws_bytes, NULL) == TA_ERR_INVALID_SHAPE,
+           "ssd forward, every size the largest");
+}
+
+/* The host helpers over all pairs of ordinary and extreme sizes: a status and
+   a value in range, no overflow on the way */
+static void check_extreme_sizes(void)
+{
+    const int v[] = {-1, 0, 1, 2, 16, 127, 128, 4096, 8191, 1 << 20, 1 << 24, BIG_128, BIG - 1, BIG};
+    const int nv = (int)(sizeof v / sizeof v[0]);
+    for (int i = 0; i < nv; ++i)
+        for (int j = 0; j < nv; ++j)
+            for (int k = 0; k < nv; ++k) {
+                const int a = v[i], b = v[j], c = v[k];
+                int n = 0, ok;
+                size_t bytes = 0;
+                for (int D = 64; D <= 128; D += 64)
+                    for (int g = 1; g <= 3; g += 2) {
+                        /* (g query heads per key/value head where that fits) */
+                        const int hq = b > 0 && b <= BIG / g ? b * g : b;
+                        ok = ta_split_heuristic(a, hq, b, 1, c, D, 0, &n);
+                        EXPECT(ok != TA_OK || (n >= 1 && n <= 128), "split heuristic %d %d %d", a, b, c);
+                        ok = ta_split_plan(a, hq, b, 1, c, D, 0, &n);
+                        EXPECT(ok != TA_OK || (n >= 1 && n <= 128), "split plan %d %d %d", a, b, c);
+                        ok = ta_decode_route(a, hq, b, 1, c, D, 128, &n);
+                        EXPECT(ok != TA_OK || n == 0 || n == 1, "decode route %d %d %d", a, b, c);
+                        ok = ta_decode_route(a, hq, b, c, c, D, 1, &n);
+                        EXPECT(ok != TA_OK || n == 0 || n == 1, "decode route %d %d %d", a, b, c);
+                    }
+                ok = mla_split_heuristic(a, b, b, c, &n);
+                EXPECT(ok != TA_OK || (n >= 1 && n <= 128), "mla heuristic %d %d %d", a, b, c);
+                ok = mla_split_plan(a, b, b, c, &n);
+                EXPECT(ok != TA_OK || (n >= 1 && n <= 128), "mla plan %d %d %d", a, b, c);
+                ok = mla_split_plan(a, b, 1, c, &n);
+                EXPECT(ok != TA_OK || (n >= 1 && n <= 128), "mla plan, one latent head %d %d %d", a, b, c);
+                ok = gemm_split_heuristic(a, b, c, &n);
+                EXPECT(ok != TA_OK || (n >= 1 && n <= 64), "gemm heuristic %d %d %d", a, b, c);
+                ok = gemm_split_workspace_bytes(a, b, 64, &bytes);
+                EXPECT(ok == (a > 0 && b > 0 ? TA_OK : TA_ERR_INVALID_SHAPE), "gemm workspace %d %d", a, b);
+                ok = gemv_split_heuristic(a, b, &n);
+                EXPECT(ok != TA_OK || (n >= 1 && n <= 64), "gemv heuristic %d %d", a, b);
+                ok = ssd_segment_heuristic(a, b, c, &n);
+                EXPECT(ok != TA_OK || (n >= 1 && n <= 64), "segments %d %d %d", a, b, c);
+                ok = ssd_forward_workspace_bytes(a, b, c, 64, &bytes);
+                EXPECT(ok == (a > 0 && b > 0 && c > 0 ? TA_OK : TA_ERR_INVALID_SHAPE),
+                       "ssd workspace %d %d %d", a, b, c);
+            }
+    int n;
+    EXPECT(ta_split_plan(8, 32, 8, 1, 8191, 128, 0, NULL) == TA_ERR_NULL_POINTER, "plan null");
+    EXPECT(ta_decode_route(8, 32, 8, 1, 8191, 128, 1, NULL) == TA_ERR_NULL_POINTER, "route null");
+    EXPECT(ta_decode_route(8, 32, 8, 1, 8191, 96, 1, &n) == TA_ERR_UNSUPPORTED, "route D");
+    EXPECT(mla_split_plan(8, 32, 3, 64, &n) == TA_ERR_INVALID_SHAPE, "mla plan heads");
+}
+
 int main(void)
 {
+    check_split_gemm_and_forward();
+    check_extreme_sizes();
     check_attn_validation();
     check_schedule();
     check_host_helpers();
