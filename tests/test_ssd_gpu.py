@@ -149,6 +149,11 @@ def test_state_passing(ta, shape):
     check(f"state_passing final {shape}", final.cpu().numpy(), rf, sf, bound=1e-5, rms=None)
 
 
+def chained(ta, dx, ddt, dA, dB, dC, dD=None):
+    prev, final = ta.ssd_state_passing(ta.ssd_chunk_state(dx, dB, ddt, dA), ddt, dA)
+    return ta.ssd_chunk_scan(dx, dC, ta.ssd_bmm_chunk(dC, dB), ddt, dA, prev, dD), final
+
+
 def chained_scale(inp):
     """The chained sums with every term replaced by its magnitude."""
     ab = lambda u: np.ascontiguousarray(u) & np.uint16(0x7FFF)
@@ -161,16 +166,22 @@ def chained_scale(inp):
 @pytest.mark.parametrize("shape", [(2, 300, 4, 2), (2, 1000, 8, 2), (1, 2048, 4, 1)],
                          ids=["s300", "s1000", "s2048"])
 def test_chained_forward_matches_oracle(ta, shape):
-    """The four kernels chained on the GPU reproduce the oracle's chained
-    result (pinned to the step-by-step recurrence)."""
+    """ssd_forward, and the four kernels chained on the GPU, reproduce the
+    oracle's chained result (pinned to the step-by-step recurrence)."""
     print(f"ssd chained {shape}", flush=True)
     w, inp = problem(shape, seed=17 + sum(shape))
-    y, final = ta.ssd_forward(dev_bf16(inp["x"]), dev_f32(inp["dt"]), dev_f32(inp["A"]),
-                              dev_bf16(inp["Bm"]), dev_bf16(inp["Cm"]), dev_f32(inp["D"]))
+    args = (dev_bf16(inp["x"]), dev_f32(inp["dt"]), dev_f32(inp["A"]),
+            dev_bf16(inp["Bm"]), dev_bf16(inp["Cm"]), dev_f32(inp["D"]))
+    y, final = ta.ssd_forward(*args)
+    cy, cfinal = chained(ta, *args)
     torch.cuda.synchronize()
     ry, rf = ossd.ssd_forward(inp["x"], inp["dt"], inp["A"], inp["Bm"], inp["Cm"], inp["D"], Q)
-    check(f"chained y {shape}", y.cpu().numpy(), ry, chained_scale(inp), bound=2.0 ** -6,
-          rms=2.0 ** -8)
+    scale = chained_scale(inp)
+    fs = ossd.state_passing(ossd.chunk_state_abs(inp["x"], inp["Bm"], inp["dt"], inp["A"], Q),
+                            inp["dt"], inp["A"], Q)[1]
+    for name, got, fin in (("one pass", y, final), ("chained", cy, cfinal)):
+        check(f"{name} y {shape}", got.cpu().numpy(), ry, scale, bound=2.0 ** -6, rms=2.0 ** -8)
+        check(f"{name} final {shape}", fin.cpu().numpy(), rf, np.maximum(fs, 1e-30))
 
 
 def test_workload_b1_s8k_sampled(ta):
@@ -316,11 +327,6 @@ def infinite_state_problem(shape, c, b, dt, A):
     return (dx, ddt, dA, dB, dC), torch.where(sign > 0, float("inf"), float("-inf"))[:, at:], at
 
 
-def chained(ta, dx, ddt, dA, dB, dC):
-    prev, final = ta.ssd_state_passing(ta.ssd_chunk_state(dx, dB, ddt, dA), ddt, dA)
-    return ta.ssd_chunk_scan(dx, dC, ta.ssd_bmm_chunk(dC, dB), ddt, dA, prev), final
-
-
 @pytest.mark.parametrize("b", [float("inf"), float("-inf")])
 @pytest.mark.parametrize("shape", [(1, 600, 2, 1), (2, 330, 256, 2)], ids=str)
 def test_forward_infinite_state_and_large_c(ta, shape, b):
@@ -352,3 +358,109 @@ def test_forward_infinite_state_over_segments(ta, shape, segments):
     assert torch.isfinite(y[:, :at]).all()
     for f in (final1, final):
         assert torch.equal(torch.isinf(f), torch.isinf(cfinal)) and not torch.isnan(f).any()
+
+
+def large_problem(B, L, H, G, dt, A):
+    """Inputs of ssd_forward drawn on the GPU: unit normals, dt and A uniform
+    between the bounds given."""
+    g = torch.Generator(device="cuda").manual_seed(B + L + H)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)
+    u = lambda lo, hi, *s: torch.rand(s, generator=g, device="cuda") * (hi - lo) + lo
+    return (r(B, L, H, 64), u(*dt, B, L, H), u(*A, H), r(B, L, G, 128), r(B, L, G, 128),
+            u(0.5, 1.5, H))
+
+
+def check_head(tag, args, y, final, b, h, lo=0, keep=0):
+    """One head of one batch element against the oracle run on it alone, from
+    position ``lo`` (its state there taken as zero) and compared from
+    ``lo + keep`` on."""
+    x, dt, A, Bm, Cm, D = args
+    grp = h // (x.shape[2] // Bm.shape[2])
+    bits = lambda a: a.contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
+    f32 = lambda a: a.contiguous().cpu().numpy()
+    one = slice(b, b + 1)
+    inp = dict(x=bits(x[one, lo:, h:h + 1]), Bm=bits(Bm[one, lo:, grp:grp + 1]),
+               Cm=bits(Cm[one, lo:, grp:grp + 1]), dt=f32(dt[one, lo:, h:h + 1]),
+               A=f32(A[h:h + 1]), D=f32(D[h:h + 1]))
+    ry, rf = ossd.ssd_forward(inp["x"], inp["dt"], inp["A"], inp["Bm"], inp["Cm"], inp["D"], Q)
+    got = f32(y[one, lo:, h:h + 1])
+    check(f"{tag} y head {h} of {b}", got[:, keep:], ry[:, keep:], chained_scale(inp)[:, keep:],
+          bound=2.0 ** -6, rms=2.0 ** -8)
+    if final is not None:
+        fs = ossd.state_passing(ossd.chunk_state_abs(inp["x"], inp["Bm"], inp["dt"], inp["A"], Q),
+                                inp["dt"], inp["A"], Q)[1]
+        check(f"{tag} final head {h} of {b}", f32(final[one, h:h + 1]), rf, np.maximum(fs, 1e-30))
+
+
+@pytest.mark.parametrize("shape", [(23, 1001, 64, 1), (23, 1001, 63, 21), (1, 130, 1 << 17, 1),
+                                   (1, 130, 1 << 17, 1 << 17)], ids=str)
+def test_forward_streamed_x(ta, shape):
+    """x and y past 512 MB together: x is read with the non-temporal policy, by
+    two heads per workgroup and by one (three heads in a group); ragged L.
+    The most heads, in one group and in as many: rows of x, y, B and C at
+    their widest (64 rows of y span 2^31 bytes)."""
+    print(f"ssd_forward streamed {shape}", flush=True)
+    B, L, H, G = shape
+    args = large_problem(B, L, H, G, (1e-3, 1e-1), (-16.0, -1.0))
+    y, final = ta.ssd_forward(*args)
+    torch.cuda.synchronize()
+    assert torch.isfinite(y).all() and torch.isfinite(final).all()
+    for b, h in ((0, 0), (0, H - 1), (B // 2, H // 2 - 1), (B - 1, H // 2), (B - 1, H - 1)):
+        check_head(f"streamed {shape}", args, y, final, b, h)
+
+
+@pytest.mark.parametrize("segments", [1, None])
+def test_forward_past_4_gib_per_batch_element(ta, segments):
+    """y of one batch element past 4 GiB, beyond what one 32-bit buffer range
+    covers: both ends of the sequence and the middle.  With these decays a
+    state is gone after 300 positions (e^-0.4 and less at each)."""
+    B, L, H, G = 1, (1 << 18) + 333, 64, 1
+    print(f"ssd_forward L={L} segments={segments}", flush=True)
+    args = large_problem(B, L, H, G, (5e-2, 1e-1), (-16.0, -8.0))
+    y, final = ta.ssd_forward(*args, num_segments=segments)
+    torch.cuda.synchronize()
+    assert torch.isfinite(y).all() and torch.isfinite(final).all()
+    first = tuple(a[:, :1000] if a.dim() > 1 else a for a in args)
+    mid = tuple(a[:, L // 2:L // 2 + 1000] if a.dim() > 1 else a for a in args)
+    for h in (0, 63):
+        check_head("first rows", first, y[:, :1000], None, 0, h)
+        check_head("middle rows", mid, y[:, L // 2:L // 2 + 1000], None, 0, h, keep=300)
+        check_head("last rows", args, y, final, 0, h, lo=L - 900, keep=300)
+
+
+def test_forward_without_final_states_and_on_a_side_stream(ta):
+    """final_states NULL through the C ABI, and a call on another stream while
+    the current one has a write queued into a freed block of the workspace's
+    size: the same y bit for bit, and the block is left alone."""
+    B, L, H, G = 1, 1000, 64, 1
+    args = large_problem(B, L, H, G, (1e-3, 1e-1), (-16.0, -1.0))
+    x, dt, A, Bm, Cm, D = args
+    y, final = ta.ssd_forward(*args)
+    n = ta.ssd_segment_heuristic(B, L, H)
+    assert n > 1
+    need = ta.ssd_forward_workspace_bytes(B, L, H, n)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    y2 = torch.full_like(y, float("nan"))
+    rc = ta.lib().ssd_forward(x.data_ptr(), Bm.data_ptr(), Cm.data_ptr(), dt.data_ptr(), A.data_ptr(),
+                              D.data_ptr(), y2.data_ptr(), None, B, L, H, G, 64, 128, n, ws.data_ptr(),
+                              need, torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    slow = torch.zeros(1 << 27, device="cuda")
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    assert torch.equal(y, y2)
+    del ws, y2
+    torch.cuda.empty_cache()
+    outputs = [torch.empty_like(y), torch.empty_like(final)]   # (blocks for the call's outputs)
+    block = torch.empty(need, dtype=torch.uint8, device="cuda")
+    where = block.data_ptr()
+    torch.cuda.synchronize()
+    for _ in range(8):
+        slow.add_(1.0)
+    block.fill_(0xFF)            # queued behind them (fp32 NaN)
+    del block, outputs
+    y3, final3 = ta.ssd_forward(*args, stream=s)
+    again = torch.empty(need, dtype=torch.uint8, device="cuda")
+    assert again.data_ptr() == where, "the current stream's block went to the call"
+    torch.cuda.synchronize()
+    assert torch.equal(y, y3) and torch.equal(final, final3)
