@@ -940,19 +940,21 @@ size_t split_workspace_bytes(int B, int Hq, int Sq, int D, int num_splits)
 // waves of a workgroup, where that is the faster one.  `wg` counts its
 // workgroups, one per (batch, key/value head, split), of which a CU holds one;
 // a tiled workgroup takes one query head, and a CU holds two or four.
-//  * Up to one workgroup per CU: always (us, tiled -> decode: B=1 Hq=4 Hkv=2
-//    Sk=100 D=64 4.5 -> 3.8; B=4 Hq=Hkv=32 Sk=3583 74 -> 47; B=16 Hq=64 Hkv=8
-//    Sk=1000 75 -> 15), but for a single whole key tile and few query heads,
-//    where the tiled kernel needs no mask (64 heads D=64 3.5 | 3.9).
+// (us, tiled | decode):
+//  * Up to one workgroup per CU: always (B=1 Hq=4 Hkv=2 Sk=100 D=64 4.5 | 3.8;
+//    B=4 Hq=Hkv=32 Sk=3583 74 | 47; B=16 Hq=64 Hkv=8 Sk=1000 75 | 15), but for a
+//    single whole key tile and few query heads, where the tiled kernel needs
+//    no mask (64 heads D=64 3.5 | 4.0).
 //  * More, with three and more query heads per key/value head: always (300
-//    workgroups of three D=64 Sk=64 6.6 -> 6.4, of eight D=128 Sk=2048 343 -> 78).
+//    workgroups of three D=64 Sk=64 6.9 | 6.3, of eight D=128 Sk=2048 270 | 62).
 //  * More, with one: fill and merge of the rounds overlap nothing, so the keys
-//    have to be many (D=64, tiled | decode: 300 workgroups Sk=64 4.6 | 6.5, 256
-//    8.3 | 7.8, 512 13.3 | 11.6; 2048 workgroups Sk=128 19 | 25, 512 45 | 50, 1024
-//    98 | 85; D=128: 512 workgroups Sk=64 7 | 9, 8192 workgroups Sk=128 0.93, 256
-//    1.04 times as fast; 1536 workgroups Sk=256 0.89, 448 1.08), and at D = 128
-//    a second round of fewer than 64 gains nothing at any length (0.95-1.02).
-//  * More, with two: one key tile at D = 64 is too short (0.82-1.0).
+//    have to be many (D=64: 300 workgroups Sk=64 4.6 | 6.5, 512 13.3 | 11.6; 2048
+//    workgroups Sk=128 19 | 25, 512 45 | 50, 1024 98 | 85; 8192 workgroups Sk=64
+//    40 | 84; D=128: 2048 workgroups Sk=64 22 | 25, 256 46 | 51, 384 77 | 68), and
+//    at D = 128 a second round of fewer than 64 gains nothing at any length
+//    (300 workgroups Sk=1024 31.5 | 33.0, 2048 58.7 | 61.1).
+//  * More, with two: one key tile at D = 64 is too short (0.82 to 1.0 times as
+//    fast).
 // And a launch counts its threads in 32 bits: the tiled kernel, whose
 // workgroups are smaller, takes the calls with too many for one launch.
 bool is_decode(int64_t wg, int group, int Sq, int64_t keys, int D)
