@@ -250,13 +250,13 @@ def _scratch(shape, dtype, t, stream):
     stream's could still be in use by work queued there, or be given to such
     work, while the launch on ``stream`` runs."""
     if stream is None:
-        return torch.empty(shape, dtype=dtype, device=t.device)
+        return t.new_empty(shape, dtype=dtype)
     with torch.cuda.stream(stream):
-        return torch.empty(shape, dtype=dtype, device=t.device)
+        return t.new_empty(shape, dtype=dtype)
 
 
 def _workspace(need, t, stream):
-    return _scratch((max(need, 16),), torch.uint8, t, stream)
+    return _scratch(max(need, 16), torch.uint8, t, stream)
 
 
 def _attn(q, k, v, causal, scale, out, lse, stream, o_dtype, raw):
