@@ -667,10 +667,10 @@ __global__ __launch_bounds__(NT, 4) void state_passing_kernel(PassArgs args)
 // times and x twice, 9.7 GB at B=64 L=2048 H=64 where x, Bm, Cm, dt and y are
 // 3.5.  Here a workgroup of four waves walks the sequence of one or two heads
 // (NH) of a group in steps of FQ = 64 positions with the state in registers
-// (fp32), so x is read and y written once and nothing else moves: 2.07 ms ->
-// 0.97 ms there.  The same traffic without the arithmetic takes 0.58 ms, the
+// (fp32), so x is read and y written once and nothing else moves: 2.06 ms ->
+// 0.93 ms there.  The same traffic without the arithmetic takes 0.58 ms, the
 // arithmetic without the stores 0.75: what bounds it is the instructions of
-// the two waves that share a SIMD (VALU issue 46 %, matrix cores 28 % of the
+// the two waves that share a SIMD (VALU issue 43 %, matrix cores 27 % of the
 // time) and their waits on each other.
 //  * A head's state S^T[n][p] and y^T[p][l] are split over 4 / NH waves, 16 NH
 //    head dims each (16 x 16 accumulator blocks, lane = dim p of the state,
