@@ -453,7 +453,7 @@ def gemm_bf16(a, b, out=None, out_dtype=None, stream=None, num_splits: int | Non
     float32 (default) or bfloat16 (``out_dtype=torch.bfloat16``).  K is
     summed in ``num_splits`` ranges (default gemm_split_heuristic: one unless
     the product has few tiles and a long K), through a workspace allocated
-    here."""
+    here; the default is one range where there is no memory for it."""
     for name, t in (("a", a), ("b", b)):
         if t.dtype != torch.bfloat16 or not t.is_cuda or t.dim() != 2 or not t.is_contiguous():
             raise TypeError(f"{name} must be a contiguous 2-D bfloat16 GPU tensor")
@@ -465,13 +465,18 @@ def gemm_bf16(a, b, out=None, out_dtype=None, stream=None, num_splits: int | Non
     if dt not in (torch.float32, torch.bfloat16):
         raise TypeError("out_dtype must be torch.float32 or torch.bfloat16")
     out = _output("out", out, (M, N), dt, a)
-    if num_splits is None:
+    ws, need, chosen = None, 0, num_splits is None
+    if chosen:
         # (only products of at most 256 tiles of 128 x 128 are ever split)
         num_splits = gemm_split_heuristic(M, N, K) if M > 1 and 1 <= M * N <= 256 << 14 and K > 0 else 1
-    ws, need = None, 0
     if num_splits != 1:
         need = gemm_split_workspace_bytes(M, N, num_splits)
-        ws = _workspace(need, a, stream)
+        try:
+            ws = _workspace(need, a, stream)
+        except torch.OutOfMemoryError:
+            if not chosen:
+                raise
+            # the caller asked for no workspace: one range needs none
     with _one_device(a, b, out):
         if ws is None:
             rc = gemm_bf16_raw(a.data_ptr(), b.data_ptr(), out.data_ptr(), dt == torch.bfloat16,

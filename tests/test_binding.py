@@ -131,6 +131,21 @@ def test_scratch_is_allocated_on_the_launch_stream(fake, name, side):
     assert len(fake.made) == n + outputs
 
 
+def test_gemm_without_memory_for_the_split(fake, monkeypatch):
+    """gemm_bf16(a, b, out=c) needs no memory of its own: where the workspace
+    of the count it chooses cannot be had, it runs unsplit.  A count that the
+    caller chose raises."""
+    def full(*args):
+        raise torch.OutOfMemoryError("full")
+
+    monkeypatch.setattr(ta, "_scratch", full)
+    args = t(384, 8256), t(8256, 4224), t(384, 4224, dtype=F32)
+    assert ta.gemm_bf16(*args) is args[2]
+    assert [name for name, _ in fake.calls] == ["gemm_bf16"]
+    with pytest.raises(torch.OutOfMemoryError):
+        ta.gemm_bf16(*args, num_splits=5)
+
+
 def test_ssd_calls_take_a_false_stream_as_the_current_one(fake):
     """stream=0 means the current stream to the SSD functions."""
     x, dt, A, Bm, Cm = ssd_args(1, 300, 4, 2)
