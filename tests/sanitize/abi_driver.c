@@ -245,6 +245,16 @@ static void check_other_validation(void)
     EXPECT(gemm_bf16(P(0x10000000), P(0x30000000), P(0x50000000), 0, 256, 65536, 16384, NULL) ==
                TA_ERR_INVALID_SHAPE,
            "gemm 32-bit offsets");
+    /* gemv_bf16_split */
+    EXPECT(gemv_bf16_split(P(0x10000000), P(0x30000000), P(0x50000000), 0, 256, 128, 2, NULL, 0, NULL) ==
+               TA_ERR_WORKSPACE,
+           "gemv without workspace");
+    EXPECT(gemv_bf16_split(P(0x10000000), P(0x30000000), P(0x50000000), 0, 100, 128, 2,
+                           P(0x60000000), 1u << 20, NULL) == TA_ERR_UNSUPPORTED,
+           "gemv N");
+    EXPECT(gemv_bf16_split(P(0x10000000), P(0x30000000), P(0x30000000), 0, BIG - 63, BIG - 7, 2,
+                           P(0x60000000), 1u << 20, NULL) == TA_ERR_ALIASING,
+           "gemv aliasing, the largest sizes");
     /* SSD */
     EXPECT(ssd_chunk_scan(P(0x10000000), P(0x12000000), (const float *)P(0x20000000),
                           (const float *)P(0x13000000), (const float *)P(0x14000000),
@@ -356,6 +366,13 @@ static void check_extreme_sizes(void)
                 EXPECT(ok != TA_OK || (n >= 1 && n <= 64), "gemm heuristic %d %d %d", a, b, c);
                 ok = gemm_split_workspace_bytes(a, b, 64, &bytes);
                 EXPECT(ok == (a > 0 && b > 0 ? TA_OK : TA_ERR_INVALID_SHAPE), "gemm workspace %d %d", a, b);
+                ok = gemv_split_workspace_bytes(a, 7, &bytes);
+                EXPECT(ok == (a > 0 ? TA_OK : TA_ERR_INVALID_SHAPE), "gemv workspace %d", a);
+                ok = mla_workspace_bytes(a, b, 128, &bytes);
+                EXPECT(ok == (a > 0 && b > 0 ? TA_OK : TA_ERR_INVALID_SHAPE), "mla workspace %d %d", a, b);
+                ok = ta_split_workspace_bytes(a, b, c, 128, 128, &bytes);
+                EXPECT(ok == (a > 0 && b > 0 && c > 0 ? TA_OK : TA_ERR_INVALID_SHAPE),
+                       "split workspace %d %d %d", a, b, c);
                 ok = gemv_split_heuristic(a, b, &n);
                 EXPECT(ok != TA_OK || (n >= 1 && n <= 64), "gemv heuristic %d %d", a, b);
                 ok = ssd_segment_heuristic(a, b, c, &n);

@@ -134,10 +134,9 @@ def test_split_rejects_small_workspace(ta):
 
 def test_split_side_stream_with_its_own_workspace(ta):
     """attn_fwd_split and mla_decode on a non-default stream, each allocating
-    its workspace: the same bits as on the default stream, while the default
-    stream allocates and fills memory of the workspace's size right after the
-    launch (the freed workspace block must not be handed to it before the
-    side-stream kernels have finished)."""
+    its workspace (on that stream): the same bits as on the default stream,
+    while the default stream allocates and fills memory of the workspace's
+    size right after the launch, which must not be the workspace's block."""
     q, k, v = (dev(a) for a in gen.random_problem(2, 8, 8, 512, 4000, 128, seed=31))
     o_ref, l_ref = ta.attn_fwd_split(q, k, v, num_splits=6)
     mq, mqp, mkv, mkp = (dev(a) for a in gen.random_mla_problem(4, 128, 1, 3000, seed=32))
@@ -145,8 +144,8 @@ def test_split_side_stream_with_its_own_workspace(ta):
     need = max(ta.ta_split_workspace_bytes(2, 8, 512, 128, 6), ta.mla_workspace_bytes(4, 128, 5))
     s = torch.cuda.Stream()
     s.wait_stream(torch.cuda.current_stream())
-    # launched on s from the default stream: outputs and workspaces are
-    # allocated on the default stream, whose next allocation follows
+    # launched on s from the default stream: the outputs are allocated on the
+    # default stream, whose next allocation follows, the workspaces on s
     o, lse = ta.attn_fwd_split(q, k, v, num_splits=6, stream=s)
     mo, ml = ta.mla_decode(mq, mqp, mkv, mkp, num_splits=5, stream=s)
     junk = torch.full((need // 4 + 1,), float("nan"), dtype=torch.float32, device="cuda")
@@ -203,3 +202,19 @@ def test_decode_route_boundaries(ta, case):
         torch.cuda.synchronize()
         assert float(np.abs(o.float().cpu().numpy() - ro).max()) <= O_TOL
         assert float(np.abs(lse.cpu().numpy() - rl).max()) <= LSE_TOL
+
+
+@pytest.mark.parametrize("case", [
+    # (B, Hq, Hkv, Sq, Sk, D, causal, splits): splits that take a call of few
+    # query rows to the tiled kernel, and the same splits with longer keys
+    (16, 4, 4, 1, 2048, 64, False, 8), (16, 4, 4, 3, 2000, 64, True, 8),
+    (16, 4, 4, 3, 4096, 64, True, 8), (75, 2, 2, 1, 1200, 128, False, 2),
+], ids=str)
+def test_decode_route_boundaries_split(ta, case):
+    B, Hq, Hkv, Sq, Sk, D, causal, splits = case
+    print(f"decode route {case} decode={ta.ta_decode_route(B, Hq, Hkv, Sq, Sk, D, splits)}", flush=True)
+    q, k, v = gen.random_problem(B, Hq, Hkv, Sq, Sk, D, seed=37)
+    o, lse = run_split(ta, q, k, v, causal, D ** -0.5, splits)
+    ro, rl = oracle.attn_fwd(q, k, v, causal, D ** -0.5)
+    assert float(np.abs(o.cpu().numpy() - ro).max()) <= O_TOL
+    assert float(np.abs(lse.cpu().numpy() - rl).max()) <= LSE_TOL
