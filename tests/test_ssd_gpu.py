@@ -393,12 +393,13 @@ def check_head(tag, args, y, final, b, h, lo=0, keep=0):
 
 
 @pytest.mark.parametrize("shape", [(23, 1001, 64, 1), (23, 1001, 63, 21), (1, 130, 1 << 17, 1),
-                                   (1, 130, 1 << 17, 1 << 17)], ids=str)
+                                   (1, 130, 1 << 17, 1 << 17), (1, 70, (1 << 17) + 1, 1)], ids=str)
 def test_forward_streamed_x(ta, shape):
     """x and y past 512 MB together: x is read with the non-temporal policy, by
     two heads per workgroup and by one (three heads in a group); ragged L.
     The most heads, in one group and in as many: rows of x, y, B and C at
-    their widest (64 rows of y span 2^31 bytes)."""
+    their widest (64 rows of y span 2^31 bytes); one head more runs the
+    functions chained."""
     print(f"ssd_forward streamed {shape}", flush=True)
     B, L, H, G = shape
     args = large_problem(B, L, H, G, (1e-3, 1e-1), (-16.0, -1.0))
